@@ -84,7 +84,8 @@ int trbt_stage_offsets(int64_t n, int nbw, int64_t *off);
 /* Bytes of device workspace the back-transformation of (n, nbw, nev) needs
  * (real: is_complex = 0, complex: 1).  The workspace holds the per-block
  * compact-WY factors the blocked kernels precompute (nbw a multiple of 16
- * up to 128); it is 0 for shapes served by the unblocked kernel.  The same workspace can be reused by any
+ * up to 128); it is 0 for shapes served by the streaming kernel (any other nbw:
+ * one reflector at a time).  The same workspace can be reused by any
  * later call with the same or smaller sizes.  Errors as for the transform
  * (-1 n, -2 nbw, -3 nev; -4 null `bytes`). */
 int trbt_workspace_bytes(int64_t n, int nbw, int64_t nev, int is_complex, size_t *bytes);
@@ -287,8 +288,8 @@ typedef struct {
  *   block_stages  16: compact-WY blocks of 16 consecutive stages on FP64
  *                 MFMA (problems with nbw in {16, 32, 48, 64}; other nbw
  *                 fall back to the streaming form); 1: every problem with
- *                 the streaming form, one reflector at a time, one lane per
- *                 column (strip_cols and waves then do not matter). */
+ *                 the streaming form, one reflector at a time (strip_cols
+ *                 and waves then do not matter). */
 typedef struct {
     int strip_cols;
     int waves;
@@ -530,7 +531,8 @@ int trans_ev_band_to_full_z_noalloc(int64_t n, int nbw, int64_t nev, const trbt_
  * the call returned TRBT_SUCCESS).
  * Arguments: 1 work (device, the workspace of such a call, aligned to
  * TRBT_WORK_ALIGN; NULL when the call ran without one -- the streaming
- * kernels have no waits -- which gives *fault = 0), 2 fault (host, out:
+ * form, whose only waits are between the waves of one workgroup and which
+ * fills the columns it gave up on with NaN -- which gives *fault = 0), 2 fault (host, out:
  * 0 or 1), 3 stream (the stream the call ran on).
  * Blocking: it synchronizes `stream` and then reads the word.  The word of
  * the banded-to-tridiagonal workspace is not this one (that call reports a

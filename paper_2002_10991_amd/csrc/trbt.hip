@@ -10,6 +10,7 @@
 
 #include "trbt.h"
 #include "trbt_device.h"
+#include "trbt_stream.h"
 
 namespace {
 
@@ -168,16 +169,11 @@ int apply(int64_t n, int nbw, int64_t nev, const double* hv, const double* ht, d
         }
 #undef TRBT_MAIN
     } else {
-        // the streaming kernel has no waits: its fault word is always clear
-        if (work && work_bytes >= sizeof(unsigned))
-            hipLaunchKernelGGL(k_zero_words, dim3(1), dim3(64), 0, st, (unsigned*)work, 1);
-        const unsigned grid = (unsigned)((nev + 63) / 64);
-        if (CPLX)
-            hipLaunchKernelGGL((k_unblocked<cd>), dim3(grid), dim3(64), 0, st, n, nbw, nev,
-                               (const cd*)hv, (const cd*)ht, (cd*)Z, ldz);
-        else
-            hipLaunchKernelGGL((k_unblocked<double>), dim3(grid), dim3(64), 0, st, n, nbw, nev,
-                               hv, ht, Z, ldz);
+        // the fault word, where the caller gave a workspace
+        unsigned* err = work && work_bytes >= sizeof(unsigned) ? (unsigned*)work : nullptr;
+        if (err) hipLaunchKernelGGL(k_zero_words, dim3(1), dim3(64), 0, st, err, 1);
+        const StreamProb p{n, nev, ldz, hv, ht, Z, 0, nbw};
+        if (stream_single(p, CPLX, nullptr, err, st) != hipSuccess) return TRBT_ERR_HIP;
     }
     return hipGetLastError() == hipSuccess ? TRBT_SUCCESS : TRBT_ERR_HIP;
 }

@@ -36,9 +36,9 @@
 // so results are deterministic) and applies the corrections.  No per-strip
 // partial sums cross memory.
 //
-// Streaming path (any nbw): one lane per column; the column's state is
-// checkpointed at the start of every 16-stage block, each block is
-// recomputed into a tape of per-reflector input rows, and the reverse sweep
+// Streaming path (any nbw): the streaming forward checkpoints the state at the
+// start of every 16-stage block; in the reverse sweep (one lane per column)
+// each block is recomputed into a tape of per-reflector input rows, and the reverse sweep
 // reduces dv and dtau over the 64 columns of a wave through LDS.
 
 #include <hip/hip_runtime.h>
@@ -48,6 +48,7 @@
 
 #include "trbt.h"
 #include "trbt_device.h"
+#include "trbt_stream.h"
 
 namespace {
 
@@ -823,8 +824,8 @@ __host__ __device__ inline int64_t blk_sbot(int64_t n, int64_t t)
     return stop - 15 > 0 ? stop - 15 : 0;
 }
 
-// Reflectors of 16-stage block t in the forward order of the unblocked
-// kernel (slot ascending, stage descending); f(k, r0, len) per reflector.
+// Reflectors of 16-stage block t in a forward order (slot ascending, stage
+// descending); f(k, r0, len) per reflector.
 template <typename F>
 __device__ inline void for_block_forward(int64_t n, int nbw, int64_t t, F&& f)
 {
@@ -859,29 +860,10 @@ __device__ inline void apply_real(double* z, const double* __restrict__ v, doubl
     for (int i = 0; i < len; ++i) z[i] = fma(-a, v[i], z[i]);
 }
 
-// Forward pass with a checkpoint of rows [sbot+1, n) at the start of every
-// block, stored row-major (row-contiguous across columns):
+// The forward pass is stream_single (trbt_stream.hip), with a checkpoint of rows
+// [sbot+1, n) before every block, stored row-major (row-contiguous across
+// columns):
 //   ck[(cb_t + r - sbot_t - 1) * nev + c],  cb_t = sum_{t' < t} (n - sbot_t' - 1).
-__global__ __launch_bounds__(64) void k_adj_stream_fwd(int64_t n, int nbw, int64_t nev,
-                                                       const double* __restrict__ hv,
-                                                       const double* __restrict__ ht,
-                                                       double* __restrict__ Z, int64_t ldz,
-                                                       double* __restrict__ ck)
-{
-    const int64_t c = (int64_t)blockIdx.x * 64 + threadIdx.x;
-    if (c >= nev) return;
-    double* z = Z + c * ldz;
-    const int64_t nblk = (n - 2 + KB - 1) / KB;
-    int64_t cb = 0;
-    for (int64_t t = 0; t < nblk; ++t) {
-        const int64_t rlo = blk_sbot(n, t) + 1;
-        for (int64_t r = rlo; r < n; ++r) ck[(cb + r - rlo) * nev + c] = z[r];
-        cb += n - rlo;
-        for_block_forward(n, nbw, t, [&](int64_t k, int64_t r0, int len) {
-            apply_real(z + r0, hv + k * nbw, ht[k], len);
-        });
-    }
-}
 
 constexpr int RCH = 32;   // dv entries reduced per LDS round
 
@@ -1227,8 +1209,9 @@ int adj_forward(int64_t n, int nbw, int64_t nev, const double* hv, const double*
             default: return TRBT_ERR_INTERNAL;
         }
     } else {
-        hipLaunchKernelGGL(k_adj_stream_fwd, dim3((unsigned)L.nwaves), dim3(64), 0, st, n, nbw,
-                           nev, hv, ht, Z, ldz, (double*)(ws + L.ckpt));
+        const StreamProb p{n, nev, ldz, hv, ht, Z, 0, nbw};
+        if (stream_single(p, false, (double*)(ws + L.ckpt), (unsigned*)ws, st) != hipSuccess)
+            return TRBT_ERR_HIP;
     }
     return hipGetLastError() == hipSuccess ? TRBT_SUCCESS : TRBT_ERR_HIP;
 }

@@ -52,23 +52,25 @@
 
 #include "trbt.h"
 #include "trbt_device.h"
+#include "trbt_stream.h"
 
 namespace {
 
 constexpr int NXCD = 8;             // XCDs of MI355X (locality only)
 constexpr int QSTRIDE = 16;         // ints between two queue counters (64 B)
-constexpr int MAX_GROUPS = 5;       // nbw 16, 32, 48, 64 blocked + streaming
+constexpr int MAX_GROUPS = 4 + STREAM_CLASSES;   // nbw 16, 32, 48, 64 blocked + streaming
 constexpr size_t HDR = 256 + MAX_GROUPS * NXCD * QSTRIDE * sizeof(int);
 
-struct BProb {   // complex problems: interleaved (re, im) doubles
+struct BProb {   // blocked groups; complex problems: interleaved (re, im) doubles
     int64_t n, nev, ldz;
     const double* hv;
     const double* ht;
     double* Z;
-    double* ws;       // packed blocks (blocked groups)
-    int64_t first;    // first pack block (blocked) / first workgroup (streaming)
-    int64_t nbw;
+    double* ws;       // packed blocks
+    int64_t first;    // first pack block
 };
+
+static_assert(sizeof(BProb) <= sizeof(StreamProb), "table sizes");
 
 struct BTask {
     int prob, strip;
@@ -135,18 +137,6 @@ __global__ __launch_bounds__(64 * NW) void k_blocked_batched(const BProb* __rest
     }
 }
 
-// Streaming form: one lane per column, problems back to back in the grid.
-template <typename T>
-__global__ __launch_bounds__(64) void k_unblocked_batched(const BProb* __restrict__ probs,
-                                                          int nprob)
-{
-    const BProb& P = probs[find_problem(probs, nprob, blockIdx.x)];
-    const int64_t col = ((int64_t)blockIdx.x - P.first) * 64 + threadIdx.x;
-    if (col >= P.nev) return;
-    unblocked_column<T>(P.n, (int)P.nbw, (const T*)P.hv, (const T*)P.ht,
-                        (T*)P.Z + col * P.ldz);
-}
-
 // --------------------------------------------------------------------------
 // Host side
 // --------------------------------------------------------------------------
@@ -155,11 +145,12 @@ size_t align_up(size_t x, size_t a) { return (x + a - 1) / a * a; }
 struct Group {
     bool blocked = false;
     int nbw = 0;                 // template band width (blocked groups)
+    int cls = 0;                 // kernel instance (streaming groups)
     std::vector<int> members;    // problem indices, in table order
     // device table offsets (bytes into the plan allocation) and sizes
     size_t off_probs = 0, off_tasks = 0, off_qbegin = 0;
     int ntasks = 0;
-    int64_t grid = 0;            // pack blocks (blocked) / streaming workgroups
+    int64_t grid = 0;            // pack blocks (blocked) / strips (streaming)
     int64_t apply_grid = 0;
 };
 
@@ -256,16 +247,10 @@ int dispatch_group(const trbt_plan& P, const Group& g, int gi, hipStream_t st, b
     unsigned* err = (unsigned*)P.dmem;
     int* qnext = (int*)(P.dmem + 256) + gi * NXCD * QSTRIDE;
     if (!g.blocked) {
-        if (!grid_only) {
-            if (P.cplx)
-                hipLaunchKernelGGL(k_unblocked_batched<cd>, dim3((unsigned)g.grid), dim3(64), 0,
-                                   st, (const BProb*)(P.dmem + g.off_probs),
-                                   (int)g.members.size());
-            else
-                hipLaunchKernelGGL(k_unblocked_batched<double>, dim3((unsigned)g.grid),
-                                   dim3(64), 0, st, (const BProb*)(P.dmem + g.off_probs),
-                                   (int)g.members.size());
-        }
+        if (!grid_only &&
+            stream_batched((const StreamProb*)(P.dmem + g.off_probs), (int)g.members.size(), g.grid,
+                           g.cls, P.cplx, err, st) != hipSuccess)
+            return TRBT_ERR_HIP;
         return TRBT_SUCCESS;
     }
     switch (g.nbw) {
@@ -286,15 +271,17 @@ int build_tables(trbt_plan& P, const std::vector<double*>& zptr)
     P.groups.clear();
     const bool stream_all = P.cfg.block_stages == 1;
     const int nbws[4] = {16, 32, 48, 64};
-    for (int gi = 0; gi < 5; ++gi) {
+    for (int gi = 0; gi < MAX_GROUPS; ++gi) {
         Group g;
-        g.blocked = gi < 4 && !stream_all;
+        g.blocked = gi < 4;
         g.nbw = gi < 4 ? nbws[gi] : 0;
+        g.cls = gi - 4;
         for (int i = 0; i < count; ++i) {
             const trbt_problem_d& p = P.probs[i];
             if (num_reflectors(p.n, p.nbw) == 0 || p.nev == 0) continue;
             const bool elig = use_blocked(p.n, p.nbw, P.cplx) && !stream_all;
-            if (g.blocked ? (elig && p.nbw == g.nbw) : (gi == 4 && !elig)) g.members.push_back(i);
+            if (g.blocked ? (elig && p.nbw == g.nbw) : (!elig && stream_class(p.nbw) == g.cls))
+                g.members.push_back(i);
         }
         if (!g.members.empty()) P.groups.push_back(g);
     }
@@ -314,21 +301,20 @@ int build_tables(trbt_plan& P, const std::vector<double*>& zptr)
             return problem_cost(P.probs[a], P.cplx) > problem_cost(P.probs[b], P.cplx);
         });
         const int np = (int)g.members.size();
-        std::vector<BProb> bp(np);
+        std::vector<BProb> bp(g.blocked ? np : 0);
+        std::vector<StreamProb> sp(g.blocked ? 0 : np);
         int64_t first = 0;
         for (int m = 0; m < np; ++m) {
             const int i = g.members[m];
             const trbt_problem_d& p = P.probs[i];
-            bp[m].n = p.n;
-            bp[m].nev = p.nev;
-            bp[m].ldz = p.ldz;
-            bp[m].hv = p.hh_v;
-            bp[m].ht = p.hh_tau;
-            bp[m].Z = zptr[i];
-            bp[m].ws = (double*)(P.dmem + P.ws_off[i]);
-            bp[m].nbw = p.nbw;
-            bp[m].first = first;
-            first += g.blocked ? blocked_num_blocks(p.n, p.nbw) : (p.nev + 63) / 64;
+            if (g.blocked) {
+                bp[m] = BProb{p.n, p.nev, p.ldz, p.hh_v, p.hh_tau, zptr[i],
+                              (double*)(P.dmem + P.ws_off[i]), first};
+                first += blocked_num_blocks(p.n, p.nbw);
+            } else {
+                sp[m] = StreamProb{p.n, p.nev, p.ldz, p.hh_v, p.hh_tau, zptr[i], first, p.nbw};
+                first += stream_strips(p.nev);
+            }
         }
         g.grid = first;
         std::vector<BTask> tasks;
@@ -366,11 +352,12 @@ int build_tables(trbt_plan& P, const std::vector<double*>& zptr)
             qbegin[NXCD] = (int)tasks.size();
         }
         g.ntasks = (int)tasks.size();
-        g.off_probs = reserve(bp.size() * sizeof(BProb));
+        g.off_probs = reserve(bp.size() * sizeof(BProb) + sp.size() * sizeof(StreamProb));
         g.off_tasks = reserve(tasks.size() * sizeof(BTask));
         g.off_qbegin = reserve(qbegin.size() * sizeof(int));
         host.resize(off);
-        memcpy(host.data() + g.off_probs, bp.data(), bp.size() * sizeof(BProb));
+        if (g.blocked) memcpy(host.data() + g.off_probs, bp.data(), bp.size() * sizeof(BProb));
+        else memcpy(host.data() + g.off_probs, sp.data(), sp.size() * sizeof(StreamProb));
         if (!tasks.empty())
             memcpy(host.data() + g.off_tasks, tasks.data(), tasks.size() * sizeof(BTask));
         memcpy(host.data() + g.off_qbegin, qbegin.data(), qbegin.size() * sizeof(int));
@@ -585,9 +572,8 @@ int tune_by_timing(trbt_plan& P)
             for (int waves : {8, 4})
                 if (cols == 16 || !P.cplx) cands.push_back({cols, waves, 16});
     }
-    // The streaming form (one lane per column, a dependent chain of K
-    // reflectors per lane) only competes on tiny problems; beyond that a
-    // single timing of it costs more than the whole plan's other candidates.
+    // The streaming form competes on tiny problems, where the slot pipeline of
+    // the blocked one never fills.
     if (!any_blocked || max_n <= 256) cands.push_back({16, 8, 1});
     trbt_plan_config best{16, 8, 16};
     double best_ms = 1e300;
@@ -653,7 +639,7 @@ int create_plan(const trbt_problem_d* probs, int count, bool cplx,
             P->ws_off[i] = off;
             off += blocked_bytes(p.n, p.nbw, cplx) - HDR_BYTES;
         }
-        tables += sizeof(BProb) + sizeof(BTask) * (size_t)((p.nev + 15) / 16);
+        tables += sizeof(StreamProb) + sizeof(BTask) * (size_t)((p.nev + 15) / 16);
     }
     P->table_off = align_up(off, 256);
     P->dbytes = P->table_off + tables + MAX_GROUPS * (3 * 256 + (NXCD + 1) * sizeof(int));

@@ -13,9 +13,7 @@
 //
 // Two device paths:
 //
-//  * unblocked ("generic"): one lane per column, every reflector applied
-//    by a dot product and an axpy on the column in global memory, in a
-//    blocked topological order of the reflector DAG.  Any nbw.
+//  * streaming (trbt_stream.hip): one reflector at a time, any nbw.
 //
 //  * blocked ("tile ring", nbw a multiple of 16, up to 64 in every form
 //    and up to 128 for the single-problem forward): the reflectors
@@ -81,83 +79,7 @@ __host__ __device__ inline int64_t num_reflectors(int64_t n, int64_t b)
     return stage_offset(n, b, n - 2);
 }
 
-// --------------------------------------------------------------------------
-// Scalar helpers
-// --------------------------------------------------------------------------
-struct cd {
-    double re, im;
-};
-
 typedef double d4 __attribute__((ext_vector_type(4)));
-
-__device__ inline double conj_mul_re(cd a, cd b) { return a.re * b.re + a.im * b.im; }  // Re(conj(a) b)
-__device__ inline double conj_mul_im(cd a, cd b) { return a.re * b.im - a.im * b.re; }  // Im(conj(a) b)
-
-// ==========================================================================
-// Unblocked kernel: one lane per column.
-// Order: 16-stage blocks from the top stage down; inside a block, slot by
-// slot (ascending), and inside a slot stage by stage (descending).  This is
-// a valid topological order of the reflector DAG for every nbw, and it
-// reuses each slot's rows for 16 consecutive reflectors.
-// ==========================================================================
-__device__ inline void apply_one(double* z, const double* __restrict__ v, double tau, int len)
-{
-    double d = 0.0;
-    for (int i = 0; i < len; ++i) d = fma(v[i], z[i], d);
-    const double a = tau * d;
-    for (int i = 0; i < len; ++i) z[i] = fma(-a, v[i], z[i]);
-}
-
-__device__ inline void apply_one(cd* z, const cd* __restrict__ v, cd tau, int len)
-{
-    double dr = 0.0, di = 0.0;
-    for (int i = 0; i < len; ++i) {
-        const cd vi = v[i], zi = z[i];
-        dr += conj_mul_re(vi, zi);
-        di += conj_mul_im(vi, zi);
-    }
-    const double ar = tau.re * dr - tau.im * di;
-    const double ai = tau.re * di + tau.im * dr;
-    for (int i = 0; i < len; ++i) {
-        const cd vi = v[i];
-        cd zi = z[i];
-        zi.re -= ar * vi.re - ai * vi.im;
-        zi.im -= ar * vi.im + ai * vi.re;
-        z[i] = zi;
-    }
-}
-
-template <typename T>
-__device__ inline void unblocked_column(int64_t n, int nbw, const T* __restrict__ hv,
-                                        const T* __restrict__ ht, T* __restrict__ z)
-{
-    const int64_t nblk = (n - 2 + 15) / 16;
-    for (int64_t t = 0; t < nblk; ++t) {
-        const int64_t stop = n - 3 - 16 * t;
-        const int64_t sbot = stop - 15 > 0 ? stop - 15 : 0;
-        const int64_t J = sweeps_in_stage(n, nbw, sbot);
-        for (int64_t j = 0; j < J; ++j) {
-            for (int64_t s = stop; s >= sbot; --s) {
-                if (j >= sweeps_in_stage(n, nbw, s)) continue;
-                const int64_t k = stage_offset(n, nbw, s) + j;
-                const int64_t r0 = s + 1 + j * nbw;
-                const int len = (int)(n - r0 < nbw ? n - r0 : nbw);
-                apply_one(z + r0, hv + k * nbw, ht[k], len);
-            }
-        }
-    }
-}
-
-template <typename T>
-__global__ __launch_bounds__(64) void k_unblocked(int64_t n, int nbw, int64_t nev,
-                                                  const T* __restrict__ hv,
-                                                  const T* __restrict__ ht, T* __restrict__ Z,
-                                                  int64_t ldz)
-{
-    const int64_t col = (int64_t)blockIdx.x * 64 + threadIdx.x;
-    if (col >= nev) return;
-    unblocked_column(n, nbw, hv, ht, Z + col * ldz);
-}
 
 // ==========================================================================
 // Blocked path
@@ -1261,7 +1183,7 @@ inline bool blocked_fits(int64_t n, int nbw, bool cplx)
 }
 
 // Problems the blocked (compact-WY, MFMA) kernels take; the rest run the
-// unblocked ones.
+// streaming one.
 inline bool use_blocked(int64_t n, int nbw, bool cplx)
 {
     return blocked_eligible(nbw) && blocked_fits(n, nbw, cplx);
