@@ -463,7 +463,7 @@ int trbt_tridiag_eigh_d(int64_t n, int64_t nev, const double *d, const double *e
  * (j = 0 .. J-1, J = max(0, n-nbw-1)) and annihilates column j below the
  * band.  The reflectors are applied in reverse generation order, each as
  * y <- y - tau_j v_j (v_j^H y) on its rows (the operation of Eq. kernel);
- * the library merges 64 consecutive reflectors into one compact-WY factor
+ * the library merges 64 (real: 128) consecutive reflectors into one compact-WY factor
  * I - V T V^H and applies it with dense products on FP64 MFMA.
  *
  * Data layout:
@@ -491,8 +491,9 @@ int trbt_band_to_full_workspace_bytes(int64_t n, int nbw, int64_t nev, int is_co
  * trbt_band_to_full_workspace_bytes), 11 stream.  J == 0 (n <= nbw+1) or
  * nev == 0 return TRBT_SUCCESS without touching Z.  Asynchronous on
  * `stream`, no allocation; TRBT_ERR_WORKSPACE when work is missing or too
- * small.  The kernels have no waits between workgroups (the fault word
- * stays clear).  Results are bitwise reproducible. */
+ * small.  The kernels never depend on a wait between workgroups (large problems
+ * keep theirs in step for the sake of the caches, for 50 us at most; the fault
+ * word stays clear).  Results are bitwise reproducible. */
 int trans_ev_band_to_full_d(int64_t n, int nbw, int64_t nev, const double *hh_v, int64_t ldv,
                             const double *hh_tau, double *Z, int64_t ldz, void *work,
                             size_t work_bytes, void *stream);

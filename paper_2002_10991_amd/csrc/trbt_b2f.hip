@@ -11,47 +11,95 @@
 //     W = V^H Z,  W' = T W,  Z <- Z - V W'     (rows [j0+nbw, n) of Z).
 //
 // Kernels:
-//  * k_b2f_tfac (one workgroup per panel): the Gram matrix V^H V on FP64
-//    MFMA, then T column by column, T[0:q, q] = -tau_q T[0:q, 0:q] G[0:q, q],
-//    stored column-major (PW x PW) in the workspace.
-//  * k_b2f_apply (one workgroup per strip of 16 CT columns of Z, NW waves):
-//    for every panel p from the last to the first, the waves walk the
-//    panel's rows in 16-row blocks (block b to wave b mod NW).  A block is
-//    loaded once into MFMA accumulators, updated with panel p
-//    (Z -= V_p W'_p, W'_p in LDS), stored, and -- while still in registers --
-//    contracted with the next panel's reflectors, W_{p-1} += V_{p-1}^H Z.
-//    So each panel reads and writes its rows of Z once.  The waves' partial
-//    W_{p-1} are summed in wave order through LDS (bitwise reproducible),
-//    multiplied by T_{p-1} on MFMA into W'_{p-1}, and the next panel starts.
+//  * k_b2f_gram (four workgroups per panel): the Gram matrix V^H V on FP64
+//    MFMA, into the workspace.
+//  * k_b2f_tfac (one workgroup per panel): T from it, in its place.
+//  * k_b2f_apply (one workgroup per strip of 16 columns of Z, 8 waves): for
+//    every panel p from the last to the first, the waves walk the panel's rows
+//    in 16-row blocks (block b to wave b mod 8).  A block is loaded once into
+//    MFMA accumulators, updated with panel p (Z -= V_p W'_p, W'_p in LDS),
+//    stored, and -- while still in registers -- contracted with the next
+//    panel's reflectors, W_{p-1} += V_{p-1}^H Z.  So each panel reads and
+//    writes its rows of Z once.  The waves' partial W_{p-1} are summed in wave
+//    order through LDS (bitwise reproducible), multiplied by T_{p-1} on MFMA
+//    into W'_{p-1}, and the next panel starts.
+//
+// What bounds it: the strips re-read the reflectors, every element twice, from
+// L2; at 16 columns that is 4 flops a byte real and 8 complex, and a CU got about
+// 20 bytes a clock out of L2 (12 TB/s over the chip).  Skipping those loads
+// (a timing-only variant) took 10.3 and 125 ms where the kernel takes 14.1
+// and 159 (real n = 8192, complex n = 16384, nev = 4096; the matrix
+// instructions alone 7.7 and 112).  Wider strips would halve the reads and leave
+// half of the CUs without one at nev = 4096; more waves on a strip than one
+// workgroup holds would need memory to add their W in.  The form before (real
+// panels of 64, loads just ahead of their use, T in one serial workgroup
+// per panel): 26.6 and 319 ms, 2.1 and 6.8 of them for T (now 0.2 and 1.2).
 //
 // Register layout of v_mfma_f64_16x16x4_f64 (A lane i+16k = A[i][k], B lane
-// j+16k = B[k][j], D lane j+16g element e = D[g+4e][j]): a 16-row block of Z
-// in accumulator layout holds rows g+4e of column j, so element e is exactly
-// the B operand of the contraction over its rows 4e..4e+3; likewise element
-// e of a W tile is the B operand for reflectors 4e..4e+3 of that tile.
+// j+16k = B[k][j], D lane j+16g element e = D[g+4e][j]): a tile in accumulator
+// layout is the B operand of four chunks as it stands, element e the chunk whose
+// four rows lane groups 0..3 hold in it.
 
 #include <hip/hip_runtime.h>
 
 #include <stdint.h>
 
 #include <mutex>
+#include <type_traits>
 
 #include "trbt.h"
 #include "trbt_device.h"
 
 namespace {
 
-constexpr int B2F_PW = 64;         // reflectors per panel
-constexpr int B2F_PT = B2F_PW / 16;
-constexpr int B2F_NW = 8;          // waves per workgroup of the apply kernel
-constexpr int B2F_HDR = 256;       // workspace header (fault word, unused here)
+constexpr int B2F_UNIT = 64;       // reflectors per 64 x 64 unit of the workspace
+constexpr int B2F_NW = 8;          // waves per workgroup
+constexpr int B2F_HDR = 256;       // workspace header: fault word (unused here), step counters
+constexpr int B2F_ROUND = 256;     // workgroups the chip holds at a time (CUs; locality only)
+constexpr int B2F_STEPS = 56;      // step counters, from byte 32 of the header
+constexpr uint64_t B2F_STEP_TICKS = 5000;   // 50 us of the 100 MHz wall clock
+
+// Reflectors per panel: a pass over Z reads and writes it once per panel, so a
+// real panel of 64 would ask for 16 flop per byte of Z, the rate at which
+// memory and the matrix cores take the same time; 128 halves that traffic.
+// Complex elements carry four times the flops for twice the bytes.
+template <bool CPLX>
+struct B2F {
+    static constexpr int PW = CPLX ? 64 : 128;
+    static constexpr int PT = PW / 16;              // 16 x 16 tiles across a panel
+    static constexpr int NC = CPLX ? 2 : 1;
+    static constexpr int TILE = 256 * NC;           // doubles per tile
+    static constexpr int64_t TP = (int64_t)PW / B2F_UNIT * B2F_UNIT * B2F_UNIT * NC;   // per panel
+};
+
+// T (and before it the Gram matrix) of a panel in its part of the workspace:
+// the tiles (a, b), a <= b, of the upper triangle, each stored as the four A
+// operand chunks of v_mfma_f64_16x16x4_f64 (chunk c, lane i + 16k: element
+// [i][4c + k]; complex: the imaginary parts 256 doubles on).  Two diagonal
+// tiles share one: that of an even b in its strictly upper part, that of the odd
+// b + 1 transposed in the strictly lower part; the diagonal is tau.  So a
+// panel of 128 takes 28 + 4 tiles, the two 64 x 64 units it has, and the first
+// 64 columns the first unit alone (all a short last panel has).
+__host__ __device__ constexpr int b2f_tile(int a, int b)   // a < b
+{
+    const int m = b / 2;
+    return 2 * m * m + (b % 2 ? 2 * m : 0) + a;
+}
+__host__ __device__ constexpr int b2f_diag_tile(int b) { return 2 * (b / 2) * (b / 2) + 4 * (b / 2) + 1; }
+
+// position of element [i][j] in a tile
+__device__ inline int b2f_pos(int i, int j) { return (j >> 2) * 64 + i + 16 * (j & 3); }
 
 __host__ __device__ inline int64_t b2f_reflectors(int64_t n, int nbw)
 {
     return (nbw >= 1 && n - nbw - 1 > 0) ? n - nbw - 1 : 0;
 }
 
-__host__ __device__ inline int64_t b2f_panels(int64_t J) { return (J + B2F_PW - 1) / B2F_PW; }
+template <bool CPLX>
+__host__ __device__ inline int64_t b2f_panels(int64_t J)
+{
+    return (J + B2F<CPLX>::PW - 1) / B2F<CPLX>::PW;
+}
 
 // one stored element: real or complex (interleaved re, im)
 template <bool CPLX>
@@ -95,25 +143,14 @@ __device__ inline void st_elt(double* __restrict__ p, int64_t idx, double re, do
 }
 
 // element (row r, reflector j) of the stored reflectors, or 0 where the
-// reflector has no entry (rows above its start j+nbw, rows >= n, j >= J)
-template <bool CPLX>
-__device__ inline Elt<CPLX> v_at(const double* __restrict__ V, int64_t ldv, int64_t n,
-                                 int nbw, int64_t J, int64_t r, int64_t j)
-{
-    Elt<CPLX> e{};
-    if (j < J && r >= j + nbw && r < n) e = ld_elt<CPLX>(V, r + j * ldv);
-    return e;
-}
-
-// The same without a branch: the load reads a clamped address inside the
-// n x J array (row min(r, n-1), column min(j, J-1)) and the value is
-// replaced by 0 where the reflector has no entry, so a block's loads can all
-// be issued before the first is needed.
+// reflector has no entry (rows above its start j+nbw, rows >= n): a load from
+// a clamped address inside the n x J array and a select.  Reflectors j >= J
+// give those of J-1; T has zeros in their rows and columns.
 template <bool CPLX>
 __device__ inline Elt<CPLX> v_sel(const double* __restrict__ V, int64_t ldv, int64_t n,
                                   int nbw, int64_t J, int64_t r, int64_t j)
 {
-    const bool ok = j < J && r >= j + nbw && r < n;
+    const bool ok = r >= j + nbw && r < n;
     const int64_t rr = r < n ? r : n - 1, jj = j < J ? j : J - 1;
     Elt<CPLX> e = ld_elt<CPLX>(V, rr + jj * ldv);
     e.re = ok ? e.re : 0.0;
@@ -121,309 +158,672 @@ __device__ inline Elt<CPLX> v_sel(const double* __restrict__ V, int64_t ldv, int
     return e;
 }
 
-// --------------------------------------------------------------------------
-// k_b2f_tfac: T of panel p (reflectors j0 .. j0+PW-1), 256 threads.
-// G = V^H V over the panel's rows (upper 16x16 tiles only, on MFMA, written
-// to the panel's T area in global memory), then T column by column in LDS
-// (thread i owns row i), then T over G.
-// --------------------------------------------------------------------------
+// D += conj(A) B or, with NEG, D -= A B, on FP64 MFMA (complex: four products).
 template <bool CPLX>
-__global__ __launch_bounds__(256) void k_b2f_tfac(int64_t n, int nbw, const double* __restrict__ V,
-                                                  int64_t ldv, const double* __restrict__ tau,
-                                                  double* __restrict__ Tw)
+__device__ inline void mma_conj(Elt<CPLX> a, double br, double bi, Tile<CPLX>& d)
 {
-    constexpr int PW = B2F_PW, PT = B2F_PT, NC = CPLX ? 2 : 1;
-    const int64_t J = b2f_reflectors(n, nbw);
-    const int64_t p = blockIdx.x;
-    const int64_t j0 = p * PW;
-    const int64_t rlo = j0 + nbw;          // first row any reflector of the panel touches
-    double* __restrict__ Tp = Tw + p * (int64_t)PW * PW * NC;
-    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-    const int i16 = lane & 15, k4 = lane >> 4;
+    d.re = mfma(a.re, br, d.re);
+    if constexpr (CPLX) {
+        d.im = mfma(a.re, bi, d.im);
+        d.re = mfma(a.im, bi, d.re);
+        d.im = mfma_n<1>(a.im, br, d.im);
+    }
+}
 
-    // upper tiles (a <= b), numbered row by row, tile w + 4t to wave w
-    constexpr int NTILE = PT * (PT + 1) / 2;
-    constexpr int MY = (NTILE + 3) / 4;
-    int ta[MY], tb[MY];
-#pragma unroll
-    for (int t = 0; t < MY; ++t) {
-        int tg = w + 4 * t, a = 0;
-        while (a < PT && tg >= PT - a) {
-            tg -= PT - a;
-            ++a;
-        }
-        ta[t] = a;           // a == PT: no tile
-        tb[t] = a + tg;
+template <bool CPLX>
+__device__ inline void mma_sub(Elt<CPLX> a, double br, double bi, Tile<CPLX>& d)
+{
+    d.re = mfma_n<1>(a.re, br, d.re);
+    if constexpr (CPLX) {
+        d.im = mfma_n<1>(a.re, bi, d.im);
+        d.re = mfma(a.im, bi, d.re);
+        d.im = mfma_n<1>(a.im, br, d.im);
     }
-    const int cnt = (NTILE - w + 3) / 4;
-    d4 gr[MY], gi[MY];
-#pragma unroll
-    for (int t = 0; t < MY; ++t) {
-        gr[t] = d4{0.0, 0.0, 0.0, 0.0};
-        gi[t] = gr[t];
+}
+
+template <bool CPLX>
+__device__ inline void mma_add(Elt<CPLX> a, double br, double bi, Tile<CPLX>& d)
+{
+    d.re = mfma(a.re, br, d.re);
+    if constexpr (CPLX) {
+        d.im = mfma(a.re, bi, d.im);
+        d.re = mfma_n<1>(a.im, bi, d.re);
+        d.im = mfma(a.im, br, d.im);
     }
-    for (int64_t r0 = rlo; r0 < n; r0 += 4) {
-        const int64_t r = r0 + k4;
+}
+
+template <bool CPLX>
+__device__ inline Tile<CPLX> tile0()
+{
+    Tile<CPLX> t;
+    t.re = d4{0.0, 0.0, 0.0, 0.0};
+    if constexpr (CPLX) t.im = t.re;
+    return t;
+}
+
+template <bool CPLX>
+__device__ inline double imag(const Tile<CPLX>& t, int e)
+{
+    if constexpr (CPLX) return t.im[e];
+    else return 0.0;
+}
+
+// --------------------------------------------------------------------------
+// k_b2f_gram: the tiles a <= b of G = V^H V of panel blockIdx.x, strictly upper
+// part, into the panel's part of the workspace.  blockIdx.y = 0, 1: the
+// diagonal quads (a, b both in the first, second half of the tiles); 2, 3: a
+// in the first half, b in the two quarters of the second (one workgroup per
+// panel and a quarter of its tiles fills the chip at a few thousand
+// reflectors).  The waves take the 16-row blocks in turn and are summed as a
+// tree in a fixed order.
+//
+// Rows in registers: lane i + 16g holds rows r0+4g .. r0+4g+3 of column i, one
+// 32-byte read.  Element e of the four lane groups is then rows r0+4g+e:
+// any four rows may form a chunk of the contraction, so the chunk e of A (conj V)
+// and of B (V) is the same register.
+// --------------------------------------------------------------------------
+template <bool CPLX, int NA, int NB, bool DIAG>
+__device__ inline void gram_part(int64_t n, int nbw, const double* __restrict__ V, int64_t ldv,
+                                 int64_t J, int64_t j0, int a0, int b0, double* __restrict__ Tp,
+                                 double* red)
+{
+    constexpr int NT = DIAG ? NA * (NA + 1) / 2 : NA * NB;
+    constexpr int NC = B2F<CPLX>::NC;
+    const int lane = threadIdx.x & 63;
+    const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int i16 = lane & 15, g4 = lane >> 4;
+    Tile<CPLX> acc[NT];
 #pragma unroll
-        for (int t = 0; t < MY; ++t) {
-            if (t >= cnt) break;
-            // A[i][k] = conj(V[r0+k][j0+16a+i]), B[k][j] = V[r0+k][j0+16b+j]
-            const Elt<CPLX> x = v_at<CPLX>(V, ldv, n, nbw, J, r, j0 + 16 * ta[t] + i16);
-            const Elt<CPLX> y = v_at<CPLX>(V, ldv, n, nbw, J, r, j0 + 16 * tb[t] + i16);
-            gr[t] = mfma(x.re, y.re, gr[t]);
-            if constexpr (CPLX) {
-                gr[t] = mfma(x.im, y.im, gr[t]);          // Re conj(x) y
-                gi[t] = mfma(x.re, y.im, gi[t]);          // Im conj(x) y
-                gi[t] = mfma_n<1>(x.im, y.re, gi[t]);
+    for (int t = 0; t < NT; ++t) acc[t] = tile0<CPLX>();
+    const int64_t lo = j0 + 16 * (DIAG ? a0 : b0) + nbw;   // first row of the part's products
+    for (int64_t r0 = (lo & ~(int64_t)15) + 16 * w; r0 < n; r0 += 16 * B2F_NW) {
+        Elt<CPLX> x[NA + (DIAG ? 0 : NB)][4];
+        const int64_t jl = j0 + 16 * (DIAG ? a0 + NA : b0 + NB) - 1;   // the part's last reflector
+        if (r0 >= jl + nbw && r0 + 16 <= n && jl < J) {
+#pragma unroll
+            for (int t = 0; t < NA + (DIAG ? 0 : NB); ++t) {
+                const int64_t j = j0 + 16 * (t < NA ? a0 + t : b0 + t - NA) + i16;
+#pragma unroll
+                for (int e = 0; e < 4; ++e) x[t][e] = ld_elt<CPLX>(V, r0 + 4 * g4 + e + j * ldv);
+            }
+        } else {
+#pragma unroll
+            for (int t = 0; t < NA + (DIAG ? 0 : NB); ++t) {
+                const int64_t j = j0 + 16 * (t < NA ? a0 + t : b0 + t - NA) + i16;
+#pragma unroll
+                for (int e = 0; e < 4; ++e)
+                    x[t][e] = v_sel<CPLX>(V, ldv, n, nbw, J, r0 + 4 * g4 + e, j);
             }
         }
-    }
-    // G tile (a, b) element e of lane l: G[16a + l/16 + 4e][16b + l%16]
-#pragma unroll
-    for (int t = 0; t < MY; ++t) {
-        if (t >= cnt) break;
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
-            const int gi_ = 16 * ta[t] + k4 + 4 * e, gj = 16 * tb[t] + i16;
-            st_elt<CPLX>(Tp, gi_ + (int64_t)gj * PW, gr[t][e], CPLX ? gi[t][e] : 0.0);
+            int t = 0;
+#pragma unroll
+            for (int b = 0; b < (DIAG ? NA : NB); ++b)
+#pragma unroll
+                for (int a = 0; a < (DIAG ? b + 1 : NA); ++a, ++t) {
+                    const Elt<CPLX> v = x[DIAG ? b : NA + b][e];
+                    mma_conj<CPLX>(x[a][e], v.re, v.im, acc[t]);
+                }
+        }
+    }
+    // sum the waves: 4..7 onto 0..3, 2..3 onto 0..1, 1 onto 0
+#pragma unroll
+    for (int h = B2F_NW / 2; h > 0; h /= 2) {
+        __syncthreads();
+        if (w >= h && w < 2 * h) {
+#pragma unroll
+            for (int t = 0; t < NT; ++t)
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    double* q = red + (((w - h) * NT + t) * NC * 4 + e) * 64 + lane;
+                    q[0] = acc[t].re[e];
+                    if constexpr (CPLX) q[256] = acc[t].im[e];
+                }
+        }
+        __syncthreads();
+        if (w < h) {
+#pragma unroll
+            for (int t = 0; t < NT; ++t)
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    const double* q = red + ((w * NT + t) * NC * 4 + e) * 64 + lane;
+                    acc[t].re[e] += q[0];
+                    if constexpr (CPLX) acc[t].im[e] += q[256];
+                }
+        }
+    }
+    if (w == 0) {
+        int t = 0;
+#pragma unroll
+        for (int b = 0; b < (DIAG ? NA : NB); ++b)
+#pragma unroll
+            for (int a = 0; a < (DIAG ? b + 1 : NA); ++a, ++t) {
+                const int ta = a0 + a, tb = b0 + b;
+                const bool dg = DIAG && a == b;
+                double* tp = Tp + (int64_t)(dg ? b2f_diag_tile(tb) : b2f_tile(ta, tb)) *
+                                      B2F<CPLX>::TILE;
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    const int i = g4 + 4 * e, j = i16;   // element [i][j] of the tile
+                    if (dg && i >= j) continue;
+                    const int pos = dg && (tb & 1) ? b2f_pos(j, i) : b2f_pos(i, j);
+                    tp[pos] = acc[t].re[e];
+                    if constexpr (CPLX) tp[256 + pos] = acc[t].im[e];
+                }
+            }
+    }
+}
+
+template <bool CPLX>
+__global__ __launch_bounds__(64 * B2F_NW) void k_b2f_gram(int64_t n, int nbw,
+                                                          const double* __restrict__ V,
+                                                          int64_t ldv, double* __restrict__ Tw)
+{
+    constexpr int H = B2F<CPLX>::PT / 2, Q = H / 2;
+    constexpr int RT = H * (H + 1) / 2 > H * Q ? H * (H + 1) / 2 : H * Q;
+    __shared__ double red[B2F_NW / 2 * RT * B2F<CPLX>::TILE];
+    const int64_t J = b2f_reflectors(n, nbw);
+    const int64_t j0 = (int64_t)blockIdx.x * B2F<CPLX>::PW;
+    double* Tp = Tw + blockIdx.x * B2F<CPLX>::TP;
+    const int y = blockIdx.y;
+    // (a short last panel has room for the first 64 columns only, and no others)
+    if (y > 0 && j0 + 16 * H >= J) return;
+    if (y < 2) gram_part<CPLX, H, H, true>(n, nbw, V, ldv, J, j0, H * y, H * y, Tp, red);
+    else gram_part<CPLX, H, Q, false>(n, nbw, V, ldv, J, j0, 0, H + Q * (y - 2), Tp, red);
+}
+
+// --------------------------------------------------------------------------
+// k_b2f_tfac: T of panel blockIdx.x in place of its Gram matrix: the forward
+// compact-WY factor T = (I + D N)^{-1} D with D = diag(tau) and N the strictly
+// upper part of G (the same T as the column recursion T[0:q, q] =
+// -tau_q T[0:q, 0:q] G[0:q, q], also for tau = 0).  One wave per 16 columns b:
+// the diagonal tiles by back substitution, one lane per column, then tile by
+// tile upwards T[a][b] = -T[a][a] sum_{a<c<=b} N[a][c] T[c][b] on FP64 MFMA (a
+// result tile is the next product's B operand as it stands).
+// --------------------------------------------------------------------------
+template <bool CPLX>
+__global__ __launch_bounds__(64 * B2F<CPLX>::PT) void k_b2f_tfac(int64_t n, int nbw,
+                                                                 const double* __restrict__ tau,
+                                                                 double* __restrict__ Tw)
+{
+    using B = B2F<CPLX>;
+    constexpr int PT = B::PT, NC = B::NC, TILE = B::TILE, NS = PT * PT / 2;
+    const int64_t J = b2f_reflectors(n, nbw);
+    const int64_t j0 = (int64_t)blockIdx.x * B::PW;
+    double* __restrict__ Tp = Tw + blockIdx.x * B::TP;
+    __shared__ double N[NS * TILE];
+    __shared__ double Td[PT][16][17][NC];
+    const int lane = threadIdx.x & 63, i16 = lane & 15, g4 = lane >> 4;
+    const int b = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const bool half = j0 + 8 * PT >= J;   // a short last panel: the first half of the tiles
+    const int ns = half ? PT * PT / 8 : NS;
+    for (int x = threadIdx.x; x < ns * TILE; x += 64 * PT) N[x] = Tp[x];
+    __syncthreads();
+    const bool act = !half || b < PT / 2;
+    if (act && lane < 16) {
+        const double* S = N + b2f_diag_tile(b) * TILE;
+        const int p = lane;
+        for (int i = 15; i >= 0; --i) {
+            const int64_t q = j0 + 16 * b + i;
+            Elt<CPLX> u{};
+            if (q < J) u = ld_elt<CPLX>(tau, q);
+            double tr = u.re, ti = u.im;
+            if (i < p) {
+                double wr = 0.0, wi = 0.0;   // sum_{k=i+1}^{p} N[i][k] T[k][p]
+                for (int k = i + 1; k <= p; ++k) {
+                    const int pos = b & 1 ? b2f_pos(k, i) : b2f_pos(i, k);
+                    const double gr = S[pos], xr = Td[b][k][p][0];
+                    if constexpr (CPLX) {
+                        const double gi = S[256 + pos], xi = Td[b][k][p][NC - 1];
+                        wr += gr * xr - gi * xi;
+                        wi += gr * xi + gi * xr;
+                    } else {
+                        wr += gr * xr;
+                    }
+                }
+                tr = -(u.re * wr - u.im * wi);
+                ti = -(u.re * wi + u.im * wr);
+            } else if (i > p) {
+                tr = ti = 0.0;
+            }
+            Td[b][i][p][0] = tr;
+            if constexpr (CPLX) Td[b][i][p][NC - 1] = ti;
         }
     }
     __syncthreads();
-
-    // T = forward compact-WY factor: T[q][q] = tau_q, and for i < q
-    // T[i][q] = -tau_q sum_{k=i}^{q-1} T[i][k] G[k][q]  (row i by thread i)
-    __shared__ double Ts[PW][PW + 1][NC];
-    const int i = threadIdx.x;
-    for (int q = 0; q < PW; ++q) {
-        if (i < PW) {
-            const int64_t jq = j0 + q;
-            Elt<CPLX> tq{};
-            if (jq < J) tq = ld_elt<CPLX>(tau, jq);
-            double sr = 0.0, si = 0.0;
-            if (i < q) {
-                for (int k = i; k < q; ++k) {
-                    const Elt<CPLX> g = ld_elt<CPLX>(Tp, k + (int64_t)q * PW);
-                    const double ar = Ts[i][k][0], ai = CPLX ? Ts[i][k][NC - 1] : 0.0;
-                    sr += ar * g.re - ai * g.im;
-                    si += ar * g.im + ai * g.re;
-                }
+    if (!act) return;
+    Tile<CPLX> t[PT];
+#pragma unroll
+    for (int c = 0; c < PT; ++c) {
+        t[c] = tile0<CPLX>();
+        if (c == b) {
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                t[c].re[e] = Td[b][g4 + 4 * e][i16][0];
+                if constexpr (CPLX) t[c].im[e] = Td[b][g4 + 4 * e][i16][NC - 1];
             }
-            double outr, outi;
-            if (i == q) {
-                outr = tq.re;
-                outi = tq.im;
-            } else if (i < q) {   // -tau_q * s
-                outr = -(tq.re * sr - tq.im * si);
-                outi = -(tq.re * si + tq.im * sr);
-            } else {
-                outr = 0.0;
-                outi = 0.0;
-            }
-            Ts[i][q][0] = outr;
-            if (CPLX) Ts[i][q][NC - 1] = outi;
         }
-        __syncthreads();
     }
-    // T over G, column-major
-    for (int idx = threadIdx.x; idx < PW * PW; idx += 256) {
-        const int r = idx % PW, c = idx / PW;
-        st_elt<CPLX>(Tp, r + (int64_t)c * PW, Ts[r][c][0], CPLX ? Ts[r][c][NC - 1] : 0.0);
+    auto chunk = [&](const double* S, int e) {
+        Elt<CPLX> v{};
+        v.re = S[e * 64 + lane];
+        if constexpr (CPLX) v.im = S[256 + e * 64 + lane];
+        return v;
+    };
+#pragma unroll
+    for (int a = PT - 2; a >= 0; --a) {
+        if (a >= b) continue;
+        Tile<CPLX> s = tile0<CPLX>();
+#pragma unroll
+        for (int c = a + 1; c < PT; ++c) {
+            if (c > b) continue;
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+                mma_add<CPLX>(chunk(N + b2f_tile(a, c) * TILE, e), t[c].re[e], imag(t[c], e), s);
+        }
+        Tile<CPLX> r = tile0<CPLX>();
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            Elt<CPLX> v{};
+            v.re = Td[a][i16][4 * e + g4][0];
+            if constexpr (CPLX) v.im = Td[a][i16][4 * e + g4][NC - 1];
+            mma_sub<CPLX>(v, s.re[e], imag(s, e), r);
+        }
+        t[a] = r;
+    }
+    // every wave has its N in LDS, so T can go over G
+#pragma unroll
+    for (int a = 0; a < PT; ++a) {
+        if (a > b) continue;
+        double* tp = Tp + (int64_t)(a == b ? b2f_diag_tile(b) : b2f_tile(a, b)) * TILE;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            const int i = g4 + 4 * e, j = i16;
+            if (a == b && i >= j) continue;
+            const int pos = a == b && (b & 1) ? b2f_pos(j, i) : b2f_pos(i, j);
+            tp[pos] = t[a].re[e];
+            if constexpr (CPLX) tp[256 + pos] = t[a].im[e];
+        }
     }
 }
 
 // --------------------------------------------------------------------------
 // k_b2f_apply
 // --------------------------------------------------------------------------
-template <bool CPLX, int CT>
+template <bool CPLX>
 struct B2FLds {
-    // W (summed partials) and W' = T W, in accumulator layout:
-    // [reflector tile][column tile][element e][plane][lane]
-    double W[B2F_PT][CT][4][CPLX ? 2 : 1][64];
-    double Wp[B2F_PT][CT][4][CPLX ? 2 : 1][64];
+    // the waves' partial W, in accumulator layout: [tile][element e][plane][lane];
+    // summed over the waves into the first
+    double W[B2F_NW][B2F<CPLX>::PT][4][B2F<CPLX>::NC][64];
+    double Wp[B2F<CPLX>::PT][4][B2F<CPLX>::NC][64];   // W' = T W
 };
 
-template <bool CPLX, int CT, int NW>
-__global__ __launch_bounds__(64 * NW) void k_b2f_apply(
-    int64_t n, int nbw, int64_t nev, const double* __restrict__ V, int64_t ldv,
-    const double* __restrict__ Tw, double* __restrict__ Z, int64_t ldz)
+// buffer resources with a scalar offset per load: no vector address arithmetic
+typedef uint32_t u4 __attribute__((ext_vector_type(4)));
+
+__device__ inline d2 buf_d2(__amdgpu_buffer_rsrc_t r, uint32_t voff, uint32_t soff)
 {
-    constexpr int PW = B2F_PW, PT = B2F_PT, NP = CPLX ? 2 : 1;
-    __shared__ B2FLds<CPLX, CT> S;
+    return __builtin_bit_cast(d2, __builtin_amdgcn_raw_buffer_load_b128(r, voff, soff, 0));
+}
+
+__device__ inline __amdgpu_buffer_rsrc_t b2f_rsrc(const double* p, int64_t bytes)
+{
+    const int64_t cap = (int64_t)1 << 31;   // offsets stay below (checked on the host)
+    return __builtin_amdgcn_make_buffer_rsrc(const_cast<double*>(p), 0,
+                                             (int)(bytes < cap ? bytes : cap - 1), 0x00020000);
+}
+
+// The strip kernel.  For every panel p from P to 0 one pass over the rows of the
+// strip: Z -= V_p W'_p (p < P, W'_p in LDS) and w = V_{p-1}^H Z (p > 0), in
+// 16-row blocks dealt to the waves in turn; then the waves' w are summed and
+// multiplied by T_{p-1}.
+//
+// Rows in registers as in k_b2f_gram: element e of lane group g is row r0+4g+e,
+// so a lane reads and writes 32 contiguous bytes of its column of Z (64
+// complex) and of the reflectors of the contraction; the update's A operand
+// takes its rows in the same order (row i of the product is r0 + 4 (i%4) + i/4).
+//
+// The blocks inside the matrix run as a pipeline: each operand register is loaded
+// again, half a block ahead, as soon as the matrix instruction that reads it has
+// been issued, and on into the wave's next block (a whole block ahead, twice
+// the registers, was slower: real 15.9 -> 18.1 ms, complex 199 -> 255 ms at the
+// sizes below).  The blocks on the slope, where reflectors start (the first
+// 2 PW rows of a pass), run in it with masks.
+//
+// FAST: two panels of reflectors fit a 32-bit byte range; otherwise every block
+// goes the slow way of a ragged last one, with 64-bit addresses.
+template <bool CPLX, bool FAST>
+__global__ __launch_bounds__(64 * B2F_NW) void k_b2f_apply(
+    int64_t n, int nbw, int64_t nev, const double* __restrict__ V, int64_t ldv,
+    const double* __restrict__ tau, const double* __restrict__ Tw, double* __restrict__ Z,
+    int64_t ldz, int* __restrict__ steps)
+{
+    using B = B2F<CPLX>;
+    constexpr int PW = B::PW, PT = B::PT, NC = B::NC, SZ = 8 * NC;
+    constexpr int NU = PW / 4, RU = NU / 2, RA = PT / 2;   // update chunks; operands in flight
+    __shared__ B2FLds<CPLX> S;
     const int64_t J = b2f_reflectors(n, nbw);
-    const int64_t P = b2f_panels(J);
+    const int64_t P = b2f_panels<CPLX>(J);
     const int lane = threadIdx.x & 63;
     const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int i16 = lane & 15, g4 = lane >> 4;
-    const int64_t col0 = (int64_t)blockIdx.x * 16 * CT;
+    const int64_t col = (int64_t)blockIdx.x * 16 + i16;
+    const bool colok = col < nev;
+    double* __restrict__ zc = Z + (colok ? col : nev - 1) * ldz * NC;
+    const int iperm = 4 * (i16 & 3) + (i16 >> 2);
+    const double* wl = &S.Wp[0][0][0][lane];
+    auto wp = [&](int c, int pl) { return wl[(c * NC + pl) * 64]; };   // chunk c of W'
 
-    Tile<CPLX> w[PT][CT];   // this wave's partial W of the next panel
+    Tile<CPLX> w[PT];   // this wave's partial W of the next panel
+#pragma unroll
+    for (int a = 0; a < PT; ++a) w[a] = tile0<CPLX>();
+    Elt<CPLX> vu[RU], va[RA][4];
+    Tile<CPLX> z;
+
+    // Workgroups of one XCD (blockIdx mod 8) and one round of the chip keep in
+    // step, panel by panel: they read the same reflectors at the same time, and
+    // once they drift apart by more than its L2 holds beside their streams of Z
+    // each fetches them again.  Only a matter of speed, so the wait is short
+    // and is given up for good when it runs out.
+    const int group = blockIdx.x / B2F_ROUND * 8 + blockIdx.x % 8;
+    const int first = blockIdx.x / B2F_ROUND * B2F_ROUND + blockIdx.x % 8;
+    const int peers = ((int)gridDim.x - first + 7) / 8 < B2F_ROUND / 8
+                          ? ((int)gridDim.x - first + 7) / 8 : B2F_ROUND / 8;
+        // Short passes drift too little to pay for it (real n = 8192: 14.1 ms without,
+    // 14.9 with; real n = 24001, nev = 2001: 163 and 135; complex n = 4096,
+    // nev = 4096: 9.8 and 10.1; complex n = 16384, nev = 4096: 184 and 159).
+    bool together = n >= (CPLX ? 6144 : 20480) && group < B2F_STEPS && peers > 1;
+    auto keep_step = [&](int need) {   // one lane
+        atomicAdd(&steps[group], 1);
+        const uint64_t t0 = wall_clock64();
+        while (__hip_atomic_load(&steps[group], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < need) {
+            __builtin_amdgcn_s_sleep(2);
+            if (wall_clock64() - t0 > B2F_STEP_TICKS) {
+                together = false;
+                break;
+            }
+        }
+    };
 
     for (int64_t p = P; p >= 0; --p) {
-        if (p < P) {
-            // ---- sum the waves' partials of W_p in wave order, then W'_p = T_p W_p
-            __syncthreads();   // every wave is done with the previous W'
-            for (int q = 0; q < NW; ++q) {
-                if (wv == q) {
-#pragma unroll
-                    for (int a = 0; a < PT; ++a)
-#pragma unroll
-                        for (int c = 0; c < CT; ++c)
-#pragma unroll
-                            for (int e = 0; e < 4; ++e) {
-                                double* sr = &S.W[a][c][e][0][lane];
-                                *sr = (q == 0) ? w[a][c].re[e] : *sr + w[a][c].re[e];
-                                if constexpr (CPLX) {
-                                    double* si = &S.W[a][c][e][NP - 1][lane];
-                                    *si = (q == 0) ? w[a][c].im[e] : *si + w[a][c].im[e];
-                                }
-                            }
-                }
-                __syncthreads();
+        const bool upd = p < P, acc = p > 0;
+        const int64_t jp = p * PW, jn = jp - PW;      // first reflectors of panels p, p-1
+        const int64_t lo = (acc ? jn : jp) + nbw;     // first row of the pass
+        int64_t r0 = (lo & ~(int64_t)15) + 16 * wv;   // this wave's first block
+        const bool pipe = FAST && r0 + 16 <= n;
+
+        // The reflectors through a buffer resource: a constant offset per lane, a
+        // scalar one per load.  Those >= J (a short last panel) read J-1's; T has
+        // zeros in their rows and columns.
+        const int64_t jb = acc ? jn : jp, je = upd ? jp + PW : jp;
+        const __amdgpu_buffer_rsrc_t rv =
+            b2f_rsrc(V + jb * ldv * NC, (((je < J ? je : J) - 1 - jb) * ldv + n) * SZ);
+        const uint32_t lb = (uint32_t)ldv * SZ;
+        const uint32_t lastc = (uint32_t)(J - 1 - jb);
+        const bool clip = FAST && je > J;
+        const uint32_t ou = (uint32_t)((jp - jb + g4) * ldv + iperm) * SZ;
+        const uint32_t oa = (uint32_t)((int64_t)i16 * ldv + 4 * g4) * SZ;
+        // chunk k of the update, V[r0 + perm][jp + 4k + g], rows from byte rb
+        auto ld_u = [&](int k, uint32_t rb) {
+            uint32_t vo = ou, so = rb + (uint32_t)(4 * k) * lb;
+            if (clip) {
+                const uint32_t c = (uint32_t)(jp - jb) + 4 * k + g4;
+                vo = (c < lastc ? c : lastc) * lb + iperm * SZ;
+                so = rb;
             }
-            const double* __restrict__ Tp = Tw + p * (int64_t)PW * PW * NP;
-            for (int t = wv; t < PT * CT; t += NW) {
-                const int a = t / CT, c = t % CT;
-                d4 accr = d4{0.0, 0.0, 0.0, 0.0}, acci = accr;
-                for (int k0 = 16 * a; k0 < PW; k0 += 4) {
-                    // A[i][k] = T[16a+i][k0+k], B[k][j] = W[k0+k][16c+j]
-                    const Elt<CPLX> tv = ld_elt<CPLX>(Tp, (16 * a + i16) + (int64_t)(k0 + g4) * PW);
-                    const int bt = k0 / 16, be = (k0 % 16) / 4;
-                    const double br = S.W[bt][c][be][0][lane];
-                    accr = mfma(tv.re, br, accr);
-                    if constexpr (CPLX) {
-                        const double bi = S.W[bt][c][be][NP - 1][lane];
-                        accr = mfma_n<1>(tv.im, bi, accr);
-                        acci = mfma(tv.re, bi, acci);
-                        acci = mfma(tv.im, br, acci);
+            if constexpr (CPLX) {
+                const d2 v = buf_d2(rv, vo, so);
+                vu[k % RU].re = v.x;
+                vu[k % RU].im = v.y;
+            } else {
+                vu[k % RU].re = buffer_load_f64(rv, vo, so);
+            }
+        };
+        // tile t of the contraction, V[r0 + 4g + e][jn + 16t + i]
+        auto ld_a = [&](int t, uint32_t rb) {
+            uint32_t vo = oa, so = rb + (uint32_t)(16 * t) * lb;
+            if (clip) {
+                const uint32_t c = 16 * t + i16;
+                vo = (c < lastc ? c : lastc) * lb + 4 * g4 * SZ;
+                so = rb;
+            }
+            if constexpr (CPLX) {
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    const d2 v = buf_d2(rv, vo + 16 * e, so);
+                    va[t % RA][e].re = v.x;
+                    va[t % RA][e].im = v.y;
+                }
+            } else {
+#pragma unroll
+                for (int e = 0; e < 4; e += 2) {
+                    const d2 v = buf_d2(rv, vo + 8 * e, so);
+                    va[t % RA][e].re = v.x;
+                    va[t % RA][e + 1].re = v.y;
+                }
+            }
+        };
+        auto ld_z = [&](int64_t r, Tile<CPLX>& x) {
+            const double* q = zc + (r + 4 * g4) * NC;
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                x.re[e] = q[e * NC];
+                if constexpr (CPLX) x.im[e] = q[e * NC + 1];
+            }
+        };
+
+        // ---- W'_p: sum the waves' partials of W_p in wave order (wave a the
+        // tile a), then W'_p = T_p W_p; meanwhile the pass's first operands
+        if (upd) {
+#pragma unroll
+            for (int a = 0; a < PT; ++a)
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    S.W[wv][a][e][0][lane] = w[a].re[e];
+                    if constexpr (CPLX) S.W[wv][a][e][NC - 1][lane] = w[a].im[e];
+                }
+        }
+        if (pipe) {
+            if (upd) {
+#pragma unroll
+                for (int k = 0; k < RU; ++k) ld_u(k, (uint32_t)r0 * SZ);
+            }
+            if (acc) {
+#pragma unroll
+                for (int t = 0; t < RA; ++t) ld_a(t, (uint32_t)r0 * SZ);
+            }
+        }
+        __syncthreads();   // (and the strip's rows are as the pass before left them)
+        if (pipe) ld_z(r0, z);
+        if (upd) {
+            if (threadIdx.x == 0 && together) keep_step(peers * (int)(P - p));
+            if (wv < PT) {
+#pragma unroll
+                for (int e = 0; e < 4; ++e)
+#pragma unroll
+                    for (int c = 0; c < NC; ++c) {
+                        double x = S.W[0][wv][e][c][lane];
+#pragma unroll
+                        for (int q = 1; q < B2F_NW; ++q) x += S.W[q][wv][e][c][lane];
+                        S.W[0][wv][e][c][lane] = x;
+                    }
+            }
+            __syncthreads();
+            if (wv < PT) {
+                // (a short last panel: T has only the first half of the tiles)
+                const int nt = jp + 8 * PT >= J ? PT / 2 : PT;
+                const double* __restrict__ Tp = Tw + p * B::TP;
+                Tile<CPLX> y = tile0<CPLX>();
+                if (wv < nt) {
+                    const double* sd = Tp + b2f_diag_tile(wv) * B::TILE;
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) {
+                        const int j = 4 * e + g4;   // element [i16][j] of the diagonal tile
+                        const int pos = wv & 1 ? b2f_pos(j, i16) : b2f_pos(i16, j);
+                        const int64_t q = jp + 16 * wv + j;
+                        const Elt<CPLX> td = ld_elt<CPLX>(tau, q < J ? q : J - 1);
+                        Elt<CPLX> v{};
+                        v.re = i16 < j ? sd[pos] : i16 == j && q < J ? td.re : 0.0;
+                        if constexpr (CPLX)
+                            v.im = i16 < j ? sd[256 + pos] : i16 == j && q < J ? td.im : 0.0;
+                        mma_add<CPLX>(v, S.W[0][wv][e][0][lane],
+                                      CPLX ? S.W[0][wv][e][NC - 1][lane] : 0.0, y);
+                    }
+                    for (int b = wv + 1; b < nt; ++b) {
+                        const double* st = Tp + b2f_tile(wv, b) * B::TILE + lane;
+#pragma unroll
+                        for (int e = 0; e < 4; ++e) {
+                            Elt<CPLX> v{};
+                            v.re = st[e * 64];
+                            if constexpr (CPLX) v.im = st[256 + e * 64];
+                            mma_add<CPLX>(v, S.W[0][b][e][0][lane],
+                                          CPLX ? S.W[0][b][e][NC - 1][lane] : 0.0, y);
+                        }
                     }
                 }
 #pragma unroll
                 for (int e = 0; e < 4; ++e) {
-                    S.Wp[a][c][e][0][lane] = accr[e];
-                    if constexpr (CPLX) S.Wp[a][c][e][NP - 1][lane] = acci[e];
+                    S.Wp[wv][e][0][lane] = y.re[e];
+                    if constexpr (CPLX) S.Wp[wv][e][NC - 1][lane] = y.im[e];
                 }
             }
             __syncthreads();
+#pragma unroll
+            for (int a = 0; a < PT; ++a) w[a] = tile0<CPLX>();
         }
-        // ---- one pass over the rows: update with panel p (if p < P), then
-        // accumulate the next panel's W (if p > 0)
+
+        // ---- the rows.  One block of the pipeline; EDGE: on the slope.
+        auto block = [&](auto edge) {
+            constexpr bool EDGE = decltype(edge)::value;
+            const int64_t rn = r0 + 16 * B2F_NW;
+            const bool more = rn + 16 <= n;
+            const uint32_t rc = (uint32_t)r0 * SZ;                  // this block
+            const uint32_t rb = (uint32_t)(more ? rn : r0) * SZ;    // the next (the last: its own again)
+            Tile<CPLX> zn;
+            ld_z(more ? rn : r0, zn);
+            asm volatile("" ::: "memory");       // W' from LDS again in every block
+            if (upd && (!EDGE || r0 + 16 > jp + nbw)) {
+                const int du = (int)(jp + nbw - r0);   // entry of row r, reflector jp+x: r - r0 - x >= du
+                Tile<CPLX> zu = z, z2 = tile0<CPLX>();
 #pragma unroll
-        for (int a = 0; a < PT; ++a)
-#pragma unroll
-            for (int c = 0; c < CT; ++c) {
-                w[a][c].re = d4{0.0, 0.0, 0.0, 0.0};
-                if constexpr (CPLX) w[a][c].im = w[a][c].re;
-            }
-        const int64_t jp = p * PW;            // first reflector of panel p
-        const int64_t jn = (p - 1) * PW;      // first reflector of panel p-1
-        const int64_t lo = (p > 0) ? jn + nbw : jp + nbw;
-        const bool upd = p < P, acc = p > 0;
-        for (int64_t r0 = lo + 16 * (int64_t)wv; r0 < n; r0 += 16 * NW) {
-            // W'_p is read from LDS block by block, not held in registers
-            // across the loop (room for the block's operands)
-            asm volatile("" ::: "memory");
-            // every load of the block first (clamped addresses, masked
-            // values), then the products
-            Tile<CPLX> z[CT];
-            // the 16-row block: lane (j, g) element e = Z[r0+g+4e][col0+16c+j]
-#pragma unroll
-            for (int c = 0; c < CT; ++c) {
-                const int64_t col = col0 + 16 * c + i16;
-                const int64_t cc = col < nev ? col : nev - 1;
+                for (int k = 0; k < NU; ++k) {
+                    Elt<CPLX> v = vu[k % RU];
+                    if (EDGE) {
+                        const bool ok = iperm - g4 >= du + 4 * k;
+                        v.re = ok ? v.re : 0.0;
+                        if constexpr (CPLX) v.im = ok ? v.im : 0.0;
+                    }
+                    if (k + RU < NU) ld_u(k + RU, rc);
+                    else ld_u(k + RU - NU, rb);
+                    mma_sub<CPLX>(v, wp(k, 0), CPLX ? wp(k, NC - 1) : 0.0,
+                                  (!CPLX && (k & 1)) ? z2 : zu);
+                }
+                if constexpr (!CPLX) zu.re += z2.re;
+                double* q = zc + (r0 + 4 * g4) * NC;
 #pragma unroll
                 for (int e = 0; e < 4; ++e) {
-                    const int64_t r = r0 + g4 + 4 * e;
-                    const bool ok = r < n && col < nev;
-                    const Elt<CPLX> x = ld_elt<CPLX>(Z, (r < n ? r : n - 1) + cc * ldz);
-                    z[c].re[e] = ok ? x.re : 0.0;
-                    if constexpr (CPLX) z[c].im[e] = ok ? x.im : 0.0;
-                }
-            }
-            const bool in_p = upd && r0 >= jp + nbw;
-            // Real blocks load all of their reflector operands before the
-            // first product (one MFMA per operand: latency would dominate);
-            // complex blocks (four MFMAs per operand, and no registers to
-            // spare) load each operand just before its products.
-            constexpr bool HOIST = !CPLX;
-            constexpr int NU = HOIST ? PW / 4 : 1, NA = HOIST ? 4 : 1, NPT = HOIST ? PT : 1;
-            // update operands: A[i][k] = V[r0+i][jp+4kk+k]
-            Elt<CPLX> vu[NU];
-            // accumulation operands: A[i][k] = conj(V[r0+4u+k][jn+16a+i])
-            Elt<CPLX> va[NA][NPT];
-            if constexpr (HOIST) {
-                if (in_p) {
-#pragma unroll
-                    for (int kk = 0; kk < PW / 4; ++kk)
-                        vu[kk] = v_sel<CPLX>(V, ldv, n, nbw, J, r0 + i16, jp + 4 * kk + g4);
-                }
-                if (acc) {
-#pragma unroll
-                    for (int u = 0; u < 4; ++u)
-#pragma unroll
-                        for (int a = 0; a < PT; ++a)
-                            va[u][a] = v_sel<CPLX>(V, ldv, n, nbw, J, r0 + 4 * u + g4,
-                                                   jn + 16 * a + i16);
-                }
-            }
-            auto v_upd = [&](int kk) -> Elt<CPLX> {
-                if constexpr (HOIST) return vu[kk];
-                else return v_sel<CPLX>(V, ldv, n, nbw, J, r0 + i16, jp + 4 * kk + g4);
-            };
-            auto v_acc = [&](int u, int a) -> Elt<CPLX> {
-                if constexpr (HOIST) return va[u][a];
-                else return v_sel<CPLX>(V, ldv, n, nbw, J, r0 + 4 * u + g4, jn + 16 * a + i16);
-            };
-            if (in_p) {
-                // Z -= V_p W'_p: A[i][k] = V[r0+i][jp+k0+k], B = W'_p rows k0..k0+3
-#pragma unroll
-                for (int k0 = 0; k0 < PW; k0 += 4) {
-                    const Elt<CPLX> v = v_upd(k0 / 4);
-                    const int bt = k0 / 16, be = (k0 % 16) / 4;
-#pragma unroll
-                    for (int c = 0; c < CT; ++c) {
-                        const double br = S.Wp[bt][c][be][0][lane];
-                        z[c].re = mfma_n<1>(v.re, br, z[c].re);
-                        if constexpr (CPLX) {
-                            const double bi = S.Wp[bt][c][be][NP - 1][lane];
-                            z[c].re = mfma(v.im, bi, z[c].re);
-                            z[c].im = mfma_n<1>(v.re, bi, z[c].im);
-                            z[c].im = mfma_n<1>(v.im, br, z[c].im);
-                        }
+                    if (EDGE && 4 * g4 + e < du) continue;   // a row above the panel's
+                    z.re[e] = zu.re[e];
+                    if constexpr (CPLX) z.im[e] = zu.im[e];
+                    if (colok) {
+                        q[e * NC] = z.re[e];
+                        if constexpr (CPLX) q[e * NC + 1] = z.im[e];
                     }
                 }
+            } else if (upd) {
 #pragma unroll
-                for (int c = 0; c < CT; ++c) {
-                    const int64_t col = col0 + 16 * c + i16;
+                for (int k = 0; k < RU; ++k) ld_u(k, rb);
+            }
+            if (acc) {
+                const int da = (int)(jn + nbw - r0);
+                if (EDGE) {
 #pragma unroll
                     for (int e = 0; e < 4; ++e) {
-                        const int64_t r = r0 + g4 + 4 * e;
-                        if (r < n && col < nev) {
-                            if constexpr (CPLX)
-                                st_elt<CPLX>(Z, r + col * ldz, z[c].re[e], z[c].im[e]);
-                            else
-                                st_elt<CPLX>(Z, r + col * ldz, z[c].re[e], 0.0);
-                        }
+                        const bool ok = 4 * g4 + e >= da;
+                        z.re[e] = ok ? z.re[e] : 0.0;
+                        if constexpr (CPLX) z.im[e] = ok ? z.im[e] : 0.0;
                     }
+                }
+#pragma unroll
+                for (int t = 0; t < PT; t += 2) {
+                    Elt<CPLX> v[2][4];
+#pragma unroll
+                    for (int e = 0; e < 4; ++e)
+#pragma unroll
+                        for (int h = 0; h < 2; ++h) {
+                            v[h][e] = va[(t + h) % RA][e];
+                            if (EDGE) {
+                                const bool ok = 4 * g4 + e - i16 >= da + 16 * (t + h);
+                                v[h][e].re = ok ? v[h][e].re : 0.0;
+                                if constexpr (CPLX) v[h][e].im = ok ? v[h][e].im : 0.0;
+                            }
+                        }
+#pragma unroll
+                    for (int h = 0; h < 2; ++h) {
+                        if (t + h + RA < PT) ld_a(t + h + RA, rc);
+                        else ld_a(t + h + RA - PT, rb);
+                    }
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) {
+                        mma_conj<CPLX>(v[0][e], z.re[e], imag(z, e), w[t]);
+                        mma_conj<CPLX>(v[1][e], z.re[e], imag(z, e), w[t + 1]);
+                    }
+                }
+            }
+            z = zn;
+            r0 = rn;
+        };
+        if constexpr (FAST) {
+            const int64_t slope = (upd ? jp : jn) + PW - 1 + nbw;   // below: every reflector's rows
+            while (r0 + 16 <= n && r0 < slope) block(std::true_type{});
+            while (r0 + 16 <= n) block(std::false_type{});
+        }
+        // ---- a ragged last block: clamped loads, masked values
+        for (; r0 < n; r0 += 16 * B2F_NW) {
+            Tile<CPLX> x;
+            int64_t r[4];
+            bool rok[4];
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                r[e] = r0 + 4 * g4 + e;
+                rok[e] = r[e] < n && r[e] >= lo;
+                const Elt<CPLX> v = ld_elt<CPLX>(zc, r[e] < n ? r[e] : n - 1);
+                x.re[e] = rok[e] ? v.re : 0.0;
+                if constexpr (CPLX) x.im[e] = rok[e] ? v.im : 0.0;
+            }
+            if (upd && r0 + 16 > jp + nbw) {
+                Tile<CPLX> zu = x;
+#pragma unroll
+                for (int h = 0; h < NU; h += RU) {
+#pragma unroll
+                    for (int k = 0; k < RU; ++k)
+                        vu[k] = v_sel<CPLX>(V, ldv, n, nbw, J, r0 + iperm, jp + 4 * (h + k) + g4);
+#pragma unroll
+                    for (int k = 0; k < RU; ++k)
+                        mma_sub<CPLX>(vu[k], wp(h + k, 0), CPLX ? wp(h + k, NC - 1) : 0.0, zu);
+                }
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    if (!rok[e] || r[e] < jp + nbw) continue;
+                    x.re[e] = zu.re[e];
+                    if constexpr (CPLX) x.im[e] = zu.im[e];
+                    if (colok) st_elt<CPLX>(zc, r[e], zu.re[e], imag(zu, e));
                 }
             }
             if (acc) {
-                // W_{p-1} += V_{p-1}^H Z: A[i][k] = conj(V[r0+4u+k][jn+16a+i]),
-                // B = element u of the block (rows 4u..4u+3)
 #pragma unroll
-                for (int u = 0; u < 4; ++u) {
+                for (int h = 0; h < PT; h += RA) {
 #pragma unroll
-                    for (int a = 0; a < PT; ++a) {
-                        const Elt<CPLX> v = v_acc(u, a);
+                    for (int t = 0; t < RA; ++t)
 #pragma unroll
-                        for (int c = 0; c < CT; ++c) {
-                            w[a][c].re = mfma(v.re, z[c].re[u], w[a][c].re);
-                            if constexpr (CPLX) {
-                                w[a][c].re = mfma(v.im, z[c].im[u], w[a][c].re);
-                                w[a][c].im = mfma(v.re, z[c].im[u], w[a][c].im);
-                                w[a][c].im = mfma_n<1>(v.im, z[c].re[u], w[a][c].im);
-                            }
-                        }
-                    }
+                        for (int e = 0; e < 4; ++e)
+                            va[t][e] = v_sel<CPLX>(V, ldv, n, nbw, J, r[e], jn + 16 * (h + t) + i16);
+#pragma unroll
+                    for (int t = 0; t < RA; ++t)
+#pragma unroll
+                        for (int e = 0; e < 4; ++e)
+                            mma_conj<CPLX>(va[t][e], x.re[e], imag(x, e), w[h + t]);
                 }
             }
         }
@@ -453,7 +853,8 @@ size_t b2f_bytes(int64_t n, int nbw, bool cplx)
 {
     const int64_t J = b2f_reflectors(n, nbw);
     if (J == 0) return 0;
-    return B2F_HDR + (size_t)b2f_panels(J) * B2F_PW * B2F_PW * (cplx ? 16 : 8);
+    const size_t units = (size_t)(J + B2F_UNIT - 1) / B2F_UNIT;
+    return B2F_HDR + units * B2F_UNIT * B2F_UNIT * (cplx ? 16 : 8);
 }
 
 template <bool CPLX>
@@ -470,25 +871,18 @@ int b2f_run(int64_t n, int nbw, int64_t nev, const double* V, int64_t ldv, const
     hipStream_t st = (hipStream_t)stream_v;
     hipLaunchKernelGGL(k_zero_words, dim3(1), dim3(64), 0, st, (unsigned*)work, 64);
     double* Tw = (double*)((char*)work + B2F_HDR);
-    const int64_t P = b2f_panels(J);
-    hipLaunchKernelGGL((k_b2f_tfac<CPLX>), dim3((unsigned)P), dim3(256), 0, st, n, nbw, V, ldv,
-                       tau, Tw);
-    // complex: two 16-column tiles per workgroup when that still gives every
-    // CU a strip; real: one (its block operands take the registers)
-    const int64_t s2 = (nev + 31) / 32;
-    if constexpr (CPLX) {
-        if (s2 >= 256) {
-            hipLaunchKernelGGL((k_b2f_apply<CPLX, 2, B2F_NW>), dim3((unsigned)s2),
-                               dim3(64 * B2F_NW), 0, st, n, nbw, nev, V, ldv, (const double*)Tw,
-                               Z, ldz);
-            return hipGetLastError() == hipSuccess ? TRBT_SUCCESS : TRBT_ERR_HIP;
-        }
-    }
-    {
-        const int64_t s1 = (nev + 15) / 16;
-        hipLaunchKernelGGL((k_b2f_apply<CPLX, 1, B2F_NW>), dim3((unsigned)s1), dim3(64 * B2F_NW),
-                           0, st, n, nbw, nev, V, ldv, (const double*)Tw, Z, ldz);
-    }
+    int* steps = (int*)((char*)work + 32);
+    using B = B2F<CPLX>;
+    const unsigned P = (unsigned)b2f_panels<CPLX>(J), strips = (unsigned)((nev + 15) / 16);
+    hipLaunchKernelGGL((k_b2f_gram<CPLX>), dim3(P, 4), dim3(64 * B2F_NW), 0, st, n, nbw, V, ldv, Tw);
+    hipLaunchKernelGGL((k_b2f_tfac<CPLX>), dim3(P), dim3(64 * B::PT), 0, st, n, nbw, tau, Tw);
+    // the pipeline addresses two panels of reflectors through a 32-bit range
+    if ((2 * B::PW + 1) * ldv * 8 * B::NC < (int64_t)1 << 31)
+        hipLaunchKernelGGL((k_b2f_apply<CPLX, true>), dim3(strips), dim3(64 * B2F_NW), 0, st, n, nbw,
+                           nev, V, ldv, tau, (const double*)Tw, Z, ldz, steps);
+    else
+        hipLaunchKernelGGL((k_b2f_apply<CPLX, false>), dim3(strips), dim3(64 * B2F_NW), 0, st, n, nbw,
+                           nev, V, ldv, tau, (const double*)Tw, Z, ldz, steps);
     return hipGetLastError() == hipSuccess ? TRBT_SUCCESS : TRBT_ERR_HIP;
 }
 
