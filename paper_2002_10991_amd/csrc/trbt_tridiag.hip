@@ -4,20 +4,18 @@
 // between the bulge chasing and the back-transformation.  Only the wanted
 // eigenvectors are computed.
 //
-// Method (the classical pair, one thread per wanted eigenpair; the paper's
-// solver is divide and conquer, which reaches the same eigenpairs):
-//   * eigenvalue i by multisection on the Sturm count: the number of
-//     negative pivots of the LDL^T factorisation of T - x I equals the number
-//     of eigenvalues below x (Sylvester's law of inertia); the interval
-//     starts from the Gershgorin bounds and is cut into 17 by 16 lanes per
-//     eigenvalue until it is no wider than a few ulps of its end points;
-//   * eigenvector i by inverse iteration with that eigenvalue: two solves
-//     (T - lambda I) x_{k+1} = x_k / ||x_k|| by Gaussian elimination with
-//     partial pivoting (the tridiagonal LU: U with two superdiagonals), from
-//     a fixed pseudo-random start; an exactly zero pivot is replaced by
-//     eps ||T||.  The factors live in the workspace, row-major across the
-//     eigenvectors, so the threads of a wave read and write consecutive
-//     addresses; the vectors are transposed into Z at the end.
+// Method (the classical pair; the paper's solver is divide and conquer, which
+// reaches the same eigenpairs):
+//   * eigenvalue i by multisection on the Sturm count: the number of sign changes
+//     in the leading principal minors of T - x I equals the number of
+//     eigenvalues below x; the interval starts from the Gershgorin bounds and is
+//     cut into 17 (33, 65) by as many lanes less one per eigenvalue until it is no
+//     wider than a few ulps of its end points;
+//   * eigenvector i by inverse iteration with that eigenvalue, one thread per
+//     vector: Gaussian elimination with partial pivoting, a half step from a
+//     fixed pseudo-random vector (the back substitution alone, as in EISPACK's
+//     tinvit) and a full step; a pivot below eps ||T|| is raised to it (so that
+//     rows equal to within rounding weigh the same in a cluster's vectors).
 // Accuracy: residual ||T x - lambda x|| ~ eps ||T||; the angle between
 // computed eigenvectors of eigenvalues a gap apart ~ eps ||T|| / gap.
 // Eigenvalues closer than 1e-6 ||T|| to their predecessor form a cluster:
@@ -31,6 +29,8 @@
 #include <math.h>
 #include <stdint.h>
 
+#include <type_traits>
+
 #include "trbt.h"
 #include "trbt_device.h"
 #include "trbt_lanes.h"
@@ -38,33 +38,21 @@
 namespace {
 
 constexpr int TD_THREADS = 64;
-constexpr int TD_ITERS = 2;
 // eigenvalues closer than this times ||T|| to their predecessor are one
 // cluster, whose vectors are orthonormalised together afterwards; outside
 // clusters the angle error of inverse iteration is below about eps / TD_CLUSTER
 constexpr double TD_CLUSTER = 1e-6;
+// floor of the squared off-diagonals of the scaled T in the Sturm counts
+constexpr double TD_E2MIN = 1e-40;
 
-// number of eigenvalues of T strictly below x
-__device__ inline int64_t sturm_count(int64_t n, const double* __restrict__ d,
-                                      const double* __restrict__ e2, double x, double pivmin)
-{
-    int64_t cnt = 0;
-    double t = d[0] - x;
-    if (fabs(t) < pivmin) t = -pivmin;
-    cnt += t < 0.0;
-    for (int64_t k = 1; k < n; ++k) {
-        t = d[k] - x - e2[k - 1] / t;
-        if (fabs(t) < pivmin) t = -pivmin;
-        cnt += t < 0.0;
-    }
-    return cnt;
-}
-
-// e2 = e^2; bounds[0..1] = Gershgorin interval, bounds[2] = max |T|-ish
-// norm estimate (max row sum), bounds[3] = pivmin.  One workgroup.
+// e2[k] = max((s e[k])^2, TD_E2MIN), re[k] = 1 / (s e[k]) (0 for 0) with s the power of
+// two that brings ||T|| into [1/2, 1); bounds[0..1] = Gershgorin interval,
+// bounds[2] = norm estimate (max row sum), bounds[3] = width below which
+// an interval is done, bounds[4] = s.  One workgroup.
 __global__ __launch_bounds__(256) void k_td_prep(int64_t n, const double* __restrict__ d,
                                                  const double* __restrict__ e,
                                                  double* __restrict__ e2,
+                                                 double* __restrict__ re,
                                                  double* __restrict__ bounds)
 {
     __shared__ double lo_s[256], hi_s[256], nm_s[256], em_s[256];
@@ -74,40 +62,125 @@ __global__ __launch_bounds__(256) void k_td_prep(int64_t n, const double* __rest
         lo = fmin(lo, d[k] - a - b);
         hi = fmax(hi, d[k] + a + b);
         nm = fmax(nm, fabs(d[k]) + a + b);
-        if (k + 1 < n) {
-            e2[k] = e[k] * e[k];
-            em = fmax(em, e2[k]);
-        }
+        em = fmax(em, b * b);
     }
     lo_s[threadIdx.x] = lo;
     hi_s[threadIdx.x] = hi;
     nm_s[threadIdx.x] = nm;
     em_s[threadIdx.x] = em;
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        for (int i = 1; i < 256; ++i) {
-            lo = fmin(lo, lo_s[i]);
-            hi = fmax(hi, hi_s[i]);
-            nm = fmax(nm, nm_s[i]);
-            em = fmax(em, em_s[i]);
+    for (int h = 128; h > 0; h /= 2) {
+        __syncthreads();
+        if (threadIdx.x < h) {
+            const int o = threadIdx.x + h;
+            lo_s[threadIdx.x] = fmin(lo_s[threadIdx.x], lo_s[o]);
+            hi_s[threadIdx.x] = fmax(hi_s[threadIdx.x], hi_s[o]);
+            nm_s[threadIdx.x] = fmax(nm_s[threadIdx.x], nm_s[o]);
+            em_s[threadIdx.x] = fmax(em_s[threadIdx.x], em_s[o]);
         }
+    }
+    __syncthreads();
+    lo = lo_s[0];
+    hi = hi_s[0];
+    nm = nm_s[0] > 0.0 ? nm_s[0] : 1.0;
+    em = em_s[0];
+    int ex;
+    (void)frexp(nm, &ex);
+    const double s = ldexp(1.0, ex < -1000 ? 1000 : -ex);
+    if (threadIdx.x == 0) {
         const double eps = 2.220446049250313e-16;
         const double pad = 2.0 * eps * fmax(fabs(lo), fabs(hi)) + 2.0 * eps * n * nm + 1e-300;
         bounds[0] = lo - pad;
         bounds[1] = hi + pad;
-        bounds[2] = nm > 0.0 ? nm : 1.0;
+        bounds[2] = nm;
         bounds[3] = fmax(2.2250738585072014e-308 * fmax(em, 1.0), 1e-290);
+        bounds[4] = s;
+    }
+    for (int64_t k = threadIdx.x; k + 1 < n; k += 256) {
+        const double es = e[k] * s;
+        e2[k] = fmax(es * es, TD_E2MIN);
+        re[k] = es != 0.0 ? 1.0 / es : 0.0;
     }
 }
 
-// eigenvalue i (0-based, ascending) by multisection: TD_MS consecutive lanes
-// share one eigenvalue and evaluate the Sturm count at TD_MS interior points
-// of its interval, x_k = lo + (hi - lo)(k+1)/(TD_MS+1); the new interval is
+// The number of eigenvalues of the scaled T below x: sign changes in the sequence
+// of its leading principal minors p_k = (d_k - x) p_{k-1} - e_{k-1}^2 p_{k-2}
+// (the pivots of LDL^T are their ratios; each computed p_k is that of a T with
+// off-diagonals changed by a few ulps).  One FMA is all that a step waits
+// for, where the pivots need a division each (350 clocks a step, 16.7 ms for the
+// 4096 lowest at n = 8192; now 57 and 2.7, most of them waits for the scalar
+// loads of d and e^2).
+//
+// The last two minors are brought back to [1/2, 1) every TD_CHUNK steps.  They
+// cannot both vanish in between: two steps leave at least the smallest
+// e^2, TD_E2MIN, of them (a change of T by 1e-20 ||T||), and none grows by more
+// than 3 a step.  A minor that is exactly zero counts once whichever sign it
+// gets, its neighbours' signs being opposite.
+constexpr int TD_CHUNK = 8;
+
+__device__ inline int td_count(int n, const double* __restrict__ d,
+                               const double* __restrict__ e2, double s, double x)
+{
+    double q = 1.0, p = fma(d[0], s, -x);   // p_{k-1}, p_k
+    unsigned bits = (unsigned)(__builtin_bit_cast(uint64_t, p) >> 63);   // signs, newest lowest
+    int cnt = (int)bits;
+    auto step = [&](double dk, double ek) {
+        const double r = fma(fma(dk, s, -x), p, -(ek * q));
+        q = p;
+        p = r;
+        bits = __builtin_amdgcn_alignbit(bits, (unsigned)(__builtin_bit_cast(uint64_t, r) >> 32), 31);
+    };
+    // whole chunks, each loaded (scalar loads: the same for every lane) while the
+    // one before is worked on
+    struct Chunk {
+        double d[TD_CHUNK], e[TD_CHUNK];
+    };
+    auto load = [&](Chunk& c, int k) {
+#pragma unroll
+        for (int i = 0; i < TD_CHUNK; ++i) {
+            c.d[i] = d[k + i];
+            c.e[i] = e2[k - 1 + i];
+        }
+    };
+    auto work = [&](const Chunk& c) {
+#pragma unroll
+        for (int i = 0; i < TD_CHUNK; ++i) step(c.d[i], c.e[i]);
+        cnt += __builtin_popcount((bits ^ (bits >> 1)) & ((1u << TD_CHUNK) - 1));
+        const int ex = __builtin_amdgcn_frexp_exp(fmax(fabs(p), fabs(q)));
+        p = __builtin_amdgcn_ldexp(p, -ex);
+        q = __builtin_amdgcn_ldexp(q, -ex);
+    };
+    const int m = (n - 1) / TD_CHUNK;
+    Chunk a, b;
+    if (m > 0) load(a, 1);
+    int j = 0;
+    for (; j + 2 < m; j += 2) {
+        load(b, 1 + (j + 1) * TD_CHUNK);
+        __builtin_amdgcn_sched_barrier(0);   // (or the loads would sink to their use)
+        work(a);
+        load(a, 1 + (j + 2) * TD_CHUNK);
+        __builtin_amdgcn_sched_barrier(0);
+        work(b);
+    }
+    if (j < m) work(a);
+    if (j + 1 < m) {
+        load(b, 1 + (j + 1) * TD_CHUNK);
+        work(b);
+    }
+    int k = 1 + m * TD_CHUNK;
+    for (; k < n; ++k) {
+        step(d[k], e2[k - 1]);
+        cnt += (bits ^ (bits >> 1)) & 1;
+    }
+    return cnt;
+}
+
+// eigenvalue i (0-based, ascending) by multisection: MS consecutive lanes share
+// one eigenvalue and evaluate the Sturm count at MS interior points of its
+// interval, x_k = lo + (hi - lo)(k+1)/(MS+1); the new interval is
 // [x_{k*-1}, x_{k*}] for the first point k* with count > i, read from the
 // group's bits of a wave ballot (every lane of the group computes the same
 // end points from the same formula).
-constexpr int TD_MS = 16;
-
+template <int MS>
 __global__ __launch_bounds__(TD_THREADS) void k_td_bisect(int64_t n, int64_t nev,
                                                           const double* __restrict__ d,
                                                           const double* __restrict__ e2,
@@ -115,27 +188,27 @@ __global__ __launch_bounds__(TD_THREADS) void k_td_bisect(int64_t n, int64_t nev
                                                           double* __restrict__ w)
 {
     const int64_t gid = (int64_t)blockIdx.x * TD_THREADS + threadIdx.x;
-    const int64_t i = gid / TD_MS;
-    const int k = (int)(gid % TD_MS);
-    const int gbit = (threadIdx.x & 63) & ~(TD_MS - 1);   // the group's first lane in the wave
+    const int64_t i = gid / MS;
+    const int k = (int)(gid % MS);
+    const int gbit = (threadIdx.x & 63) & ~(MS - 1);   // the group's first lane in the wave
     if (i >= nev) return;   // whole groups leave together
     double lo = bounds[0], hi = bounds[1];
-    const double pivmin = bounds[3];
+    const double done = bounds[3], s = bounds[4];
     const double eps = 2.220446049250313e-16;
     // invariant: count(lo) <= i < count(hi)
     for (int it = 0; it < 100; ++it) {
-        if (hi - lo <= 4.0 * eps * fmax(fabs(lo), fabs(hi)) + pivmin) break;
-        const double step = (hi - lo) / (TD_MS + 1);
+        if (hi - lo <= 4.0 * eps * fmax(fabs(lo), fabs(hi)) + done) break;
+        const double step = (hi - lo) / (MS + 1);
         const double x = lo + step * (k + 1);
-        const bool above = sturm_count(n, d, e2, x, pivmin) > i;
-        const unsigned grp = (unsigned)((__ballot(above) >> gbit) & ((1u << TD_MS) - 1));
+        const bool above = td_count((int)n, d, e2, s, x * s) > i;
+        const uint64_t grp = (__ballot(above) >> gbit) & (~0ull >> (64 - MS));
         double nlo = lo, nhi = hi;
         if (grp) {
-            const int ks = __builtin_ctz(grp);
+            const int ks = __builtin_ctzll(grp);
             nhi = lo + step * (ks + 1);
             if (ks > 0) nlo = lo + step * ks;
         } else {
-            nlo = lo + step * TD_MS;
+            nlo = lo + step * MS;
         }
         if (nlo == lo && nhi == hi) break;   // no representable progress
         lo = nlo;
@@ -144,173 +217,233 @@ __global__ __launch_bounds__(TD_THREADS) void k_td_bisect(int64_t n, int64_t nev
     if (k == 0) w[i] = 0.5 * (lo + hi);
 }
 
-// a fixed pseudo-random start in [-1, 1) (splitmix64 of (vector, row))
-__device__ inline double td_start(int64_t i, int64_t r)
+// a fixed pseudo-random start in [-1, 1): a 32-bit integer hash (two rounds of
+// multiply and xorshift, Wellons' "lowbias32") of (vector, row)
+__device__ inline double td_start(uint32_t i, uint32_t r)
 {
-    uint64_t z = (uint64_t)i * 0x9E3779B97F4A7C15ull + (uint64_t)r * 0xD1B54A32D192ED03ull + 1;
-    z = (z ^ (z >> 30)) * 0xBF58476D1CE4E5B9ull;
-    z = (z ^ (z >> 27)) * 0x94D049BB133111EBull;
-    z ^= z >> 31;
-    return (double)(z >> 11) * (2.0 / 9007199254740992.0) - 1.0;
+    uint32_t z = i * 0x9E3779B9u + r * 0x85EBCA77u + 0x7F4A7C15u;
+    z ^= z >> 16;
+    z *= 0x7FEB352Du;
+    z ^= z >> 15;
+    z *= 0x846CA68Bu;
+    z ^= z >> 16;
+    return (double)(int)z * (1.0 / 2147483648.0);
 }
 
-// eigenvector i by inverse iteration.  Row-major across the eigenvectors:
-//   X[r * nev + i]        the iterate,
-//   F[(r * 4 + q) * nev + i]  row r of the LU of T - lambda I: q = 0 the
-//                          pivot (U's diagonal), 1 and 2 U's superdiagonals,
-//                          3 the multiplier,
-//   P[r * nev + i]        1 when rows r and r+1 were swapped.
-// The recurrences run row by row, with the loads of TD_CH rows issued
-// together (one thread per eigenvector leaves few waves to hide latency).
+// 1 / x from the hardware estimate by two Newton steps (x far from the ends of
+// the range)
+__device__ inline double td_recip(double x)
+{
+    double r = __builtin_amdgcn_rcp(x);
+    r = fma(fma(-x, r, 1.0), r, r);
+    return fma(fma(-x, r, 1.0), r, r);
+}
+
+// Eigenvector i by inverse iteration on the scaled T - lambda I, one thread per
+// vector, everything row-major across the vectors (a wave reads and writes
+// consecutive addresses).  The LU factorisation with partial pivoting keeps one
+// number per row and a bit:
+//   row k not swapped with k+1 (bit 0): V = 1 / pivot; the multiplier is e_k V,
+//     U's row (pivot, b_k, 0);
+//   swapped (bit 1): V = the multiplier; U's row (e_k, d_{k+1} - lambda, e_{k+1});
+// b_k = e_k, or -V_{k-1} e_k after a swap.  Everything else comes from d and e,
+// the same for all vectors.
+//
+// Passes over the rows: the factorisation; a first half step U x = y with a
+// fixed pseudo-random y (a start b = L y, as good as a random b, and the
+// forward substitution is saved); a full step from it; the norm and the sign
+// are taken along with the second backward substitution and applied as the
+// vectors are transposed into Z.  A pass runs TD_CH rows at a time with the next
+// rows' loads already issued: nev threads are few (64 waves at nev = 4096), so
+// the issue of one wave per SIMD and its waits bound it.  n = 8192, nev = 4096:
+// 4.2 ms (19.1 with five numbers per row, a division in every substitution and
+// separate norm passes).
 constexpr int TD_CH = 16;
 
-__global__ __launch_bounds__(TD_THREADS) void k_td_invit(int64_t n, int64_t nev,
+__global__ __launch_bounds__(TD_THREADS) void k_td_invit(int64_t n64, int64_t nev,
                                                          const double* __restrict__ d,
                                                          const double* __restrict__ e,
+                                                         const double* __restrict__ re,
                                                          const double* __restrict__ bounds,
                                                          const double* __restrict__ w,
                                                          double* __restrict__ X,
-                                                         double* __restrict__ F,
-                                                         unsigned char* __restrict__ P)
+                                                         double* __restrict__ V,
+                                                         uint32_t* __restrict__ B,
+                                                         double* __restrict__ sc)
 {
     const int64_t i = (int64_t)blockIdx.x * TD_THREADS + threadIdx.x;
     if (i >= nev) return;
-    const double lam = w[i];
-    const double eps = 2.220446049250313e-16;
-    const double tiny = eps * bounds[2];
-    double* Xi = X + i;
-    double* Fi = F + i;
-    unsigned char* Pi = P + i;
-    const int64_t s4 = 4 * nev;   // stride of a row of F
+    const int n = (int)n64;
+    const double s = bounds[4];
+    const double lam = w[i] * s;
+    const double tiny = 2.220446049250313e-16 * (bounds[2] * s);
+    X += i;
+    V += i;
+    B += i;
+    auto ev = [&](int k) { return k >= 0 && k + 1 < n ? e[k] * s : 0.0; };
+    auto dv = [&](int k) { return k < n ? fma(d[k], s, -lam) : 0.0; };
 
-    // LU with partial pivoting of T - lam I.  The current row (to become
-    // U's row k, or to be swapped with row k+1) has pivot candidate a in
-    // column k and bsup in column k+1.
-    double a = d[0] - lam;
-    double bsup = n > 1 ? e[0] : 0.0;
-    for (int64_t k = 0; k + 1 < n; ++k) {
-        const double sub = e[k];                      // T(k+1, k)
-        const double dn = d[k + 1] - lam;             // T(k+1, k+1)
-        const double en = k + 2 < n ? e[k + 1] : 0.0; // T(k+1, k+2)
-        double* fr = Fi + k * s4;
-        if (fabs(a) >= fabs(sub)) {
-            const double piv = a != 0.0 ? a : tiny;
-            const double l = sub / piv;
-            fr[0] = piv;
-            fr[nev] = bsup;
-            fr[2 * nev] = 0.0;
-            fr[3 * nev] = l;
-            Pi[k * nev] = 0;
-            a = dn - l * bsup;
-            bsup = en;
-        } else {
-            const double l = a / sub;   // rows k and k+1 swapped
-            fr[0] = sub;
-            fr[nev] = dn;
-            fr[2 * nev] = en;
-            fr[3 * nev] = l;
-            Pi[k * nev] = 1;
-            a = bsup - l * dn;
-            bsup = -l * en;
-        }
-    }
+    // ---- factorisation.  The current row (to become U's row k, or to be swapped
+    // with row k+1) has a in column k and b in column k+1.
     {
-        double* fr = Fi + (n - 1) * s4;
-        fr[0] = a != 0.0 ? a : tiny;
-        fr[nev] = fr[2 * nev] = fr[3 * nev] = 0.0;
+        double a = dv(0), b = ev(0);
+        uint32_t bits = 0;
+        auto row = [&](int k, double sub, double dn, double en) {
+            const bool swap = fabs(a) < fabs(sub);
+            double x = swap ? sub : a;
+            if (fabs(x) < tiny) x = copysign(tiny, x);
+            const double r = td_recip(x);
+            const double l = (swap ? a : sub) * r;
+            V[(int64_t)k * nev] = swap ? l : r;
+            bits |= (uint32_t)swap << (k & 31);
+            a = swap ? fma(-l, dn, b) : fma(-l, b, dn);
+            b = swap ? -l * en : en;
+        };
+        int k = 0;
+        for (; k + TD_CH + 1 < n; k += TD_CH) {
+            double dc[TD_CH], ec[TD_CH + 1];
+#pragma unroll
+            for (int t = 0; t < TD_CH; ++t) {
+                dc[t] = d[k + 1 + t];
+                ec[t] = e[k + t];
+            }
+            ec[TD_CH] = e[k + TD_CH];
+#pragma unroll
+            for (int t = 0; t < TD_CH; ++t) row(k + t, ec[t] * s, fma(dc[t], s, -lam), ec[t + 1] * s);
+            if (k & 16) {
+                B[(int64_t)(k >> 5) * nev] = bits;
+                bits = 0;
+            }
+        }
+        for (; k < n; ++k) {
+            row(k, ev(k), dv(k + 1), ev(k + 1));
+            if ((k & 31) == 31 || k + 1 == n) {
+                B[(int64_t)(k >> 5) * nev] = bits;
+                bits = 0;
+            }
+        }
     }
-    for (int64_t r = 0; r < n; ++r) Xi[r * nev] = td_start(i, r);
 
-    for (int it = 0; it <= TD_ITERS; ++it) {
-        // 1 / ||x||
-        double ss = 0.0;
-        for (int64_t r0 = 0; r0 < n; r0 += TD_CH) {
-            double v[TD_CH];
+    const int nc = (n + TD_CH - 1) / TD_CH;   // chunks of TD_CH rows; a word of B holds two
+    struct Chunk {
+        double v[TD_CH + 1];   // V of the rows and (backward) of the row before
+        double y[TD_CH];
+        uint32_t bits, prev;
+    };
+    auto load = [&](Chunk& c, int q, bool before, bool withy) {
+        q = q < 0 ? 0 : q >= nc ? nc - 1 : q;
+        const int k0 = q * TD_CH;
 #pragma unroll
-            for (int q = 0; q < TD_CH; ++q) v[q] = r0 + q < n ? Xi[(r0 + q) * nev] : 0.0;
-#pragma unroll
-            for (int q = 0; q < TD_CH; ++q) ss = fma(v[q], v[q], ss);
+        for (int t = 0; t < TD_CH; ++t) {
+            const int64_t k = k0 + t < n ? k0 + t : n - 1;
+            c.v[t + 1] = V[k * nev];
+            if (withy) c.y[t] = X[k * nev];
         }
+        c.bits = B[(int64_t)(k0 >> 5) * nev];
+        if (before) {
+            const int64_t k = k0 > 0 ? k0 - 1 : 0;
+            c.v[0] = V[k * nev];
+            c.prev = B[(k >> 5) * nev];
+        }
+    };
+
+    // ---- backward substitution U x = y, in place; y random in the first
+    double ss = 0.0, big = 0.0, sg = 1.0, x1 = 0.0, x2 = 0.0;
+    auto back = [&](const Chunk& c, int q, auto first, auto edge) {
+        constexpr bool FIRST = decltype(first)::value, EDGE = decltype(edge)::value;
+        const int k0 = q * TD_CH;
+        const uint32_t cb = c.bits >> (k0 & 31);                 // bit t: row k0 + t
+        const uint32_t pb = EDGE && k0 == 0 ? 0 : c.prev >> ((k0 - 1) & 31) & 1;
+        double dc[TD_CH], ec[TD_CH + 1], rc[TD_CH];
+#pragma unroll
+        for (int t = 0; t < TD_CH; ++t) {   // rows' d_{k+1}, e_k, 1/e_k
+            const int k = k0 + t;
+            dc[t] = EDGE ? (k + 1 < n ? d[k + 1] : 0.0) : d[k + 1];
+            ec[t] = EDGE ? (k + 1 < n ? e[k] : 0.0) : e[k];
+            rc[t] = EDGE ? (k + 1 < n ? re[k] : 0.0) : re[k];
+        }
+        ec[TD_CH] = EDGE ? (k0 + TD_CH + 1 < n ? e[k0 + TD_CH] : 0.0) : e[k0 + TD_CH];
+#pragma unroll
+        for (int t = TD_CH - 1; t >= 0; --t) {
+            const int k = k0 + t;
+            if (EDGE && k >= n) continue;
+            const bool sw = cb >> t & 1, swp = t > 0 ? cb >> (t > 0 ? t - 1 : 0) & 1 : pb;
+            const double ek = ec[t] * s;
+            const double b = swp ? -c.v[t] * ek : ek;
+            const double u1 = sw ? fma(dc[t], s, -lam) : b, u2 = sw ? ec[t + 1] * s : 0.0;
+            const double ri = sw ? rc[t] : c.v[t + 1];
+            const double y = FIRST ? td_start((uint32_t)i, (uint32_t)k) : c.y[t];
+            const double x = fma(-u1, x1, fma(-u2, x2, y)) * ri;
+            X[(int64_t)k * nev] = x;
+            ss = fma(x, x, ss);
+            if (!FIRST) {   // the largest entry's sign, the first row's of equal ones
+                const bool up = fabs(x) >= big;
+                big = up ? fabs(x) : big;
+                sg = up ? (x < 0.0 ? -1.0 : 1.0) : sg;
+            }
+            x2 = x1;
+            x1 = x;
+        }
+    };
+    auto back_any = [&](const Chunk& c, int q, auto first) {
+        if (q > 0 && (q + 1) * TD_CH + 1 < n) back(c, q, first, std::false_type{});
+        else back(c, q, first, std::true_type{});
+    };
+    auto backward = [&](auto first) {
+        constexpr bool FIRST = decltype(first)::value;
+        ss = x1 = x2 = 0.0;
+        Chunk a, b;
+        load(a, nc - 1, true, !FIRST);
+        for (int q = nc - 1; q >= 0; q -= 2) {
+            load(b, q - 1, true, !FIRST);
+            back_any(a, q, first);
+            load(a, q - 2, true, !FIRST);
+            if (q > 0) back_any(b, q - 1, first);
+        }
+    };
+    backward(std::true_type{});
+
+    // ---- forward substitution: row swaps and multipliers on x / ||x||, in place
+    // (row k of the result is written once row k+1 has been read)
+    {
         const double inv = 1.0 / sqrt(ss);
-        if (it == TD_ITERS) {
-            // normalise; sign: the largest-magnitude entry positive (the
-            // first of equal ones)
-            double big = 0.0, sg = 1.0;
-            for (int64_t r0 = 0; r0 < n; r0 += TD_CH) {
-                double v[TD_CH];
+        double carry = 0.0;
+        bool sw = false;   // of row k-1
+        double l = 0.0;
+        auto forw = [&](const Chunk& c, int q, auto edge) {
+            constexpr bool EDGE = decltype(edge)::value;
+            const int k0 = q * TD_CH;
+            const uint32_t cb = c.bits >> (k0 & 31);
+            double ec[TD_CH];
 #pragma unroll
-                for (int q = 0; q < TD_CH; ++q) v[q] = r0 + q < n ? Xi[(r0 + q) * nev] : 0.0;
+            for (int t = 0; t < TD_CH; ++t) ec[t] = EDGE ? (k0 + t + 1 < n ? e[k0 + t] : 0.0) : e[k0 + t];
 #pragma unroll
-                for (int q = 0; q < TD_CH; ++q)
-                    if (fabs(v[q]) > big) {
-                        big = fabs(v[q]);
-                        sg = v[q] < 0.0 ? -1.0 : 1.0;
-                    }
+            for (int t = 0; t < TD_CH; ++t) {
+                const int k = k0 + t;
+                if (EDGE && k >= n) continue;
+                const double x = c.y[t] * inv;
+                if (!EDGE || k > 0) X[(int64_t)(k - 1) * nev] = sw ? x : carry;
+                carry = sw ? fma(-l, x, carry) : fma(-l, carry, x);   // (k = 0: x)
+                sw = cb >> t & 1;
+                l = sw ? c.v[t + 1] : ec[t] * s * c.v[t + 1];
             }
-            const double sc = sg * inv;
-            for (int64_t r = 0; r < n; ++r) Xi[r * nev] *= sc;
-            break;
+        };
+        auto forw_any = [&](const Chunk& c, int q) {
+            if (q > 0 && (q + 1) * TD_CH < n) forw(c, q, std::false_type{});
+            else forw(c, q, std::true_type{});
+        };
+        Chunk a, b;
+        load(a, 0, false, true);
+        for (int q = 0; q < nc; q += 2) {
+            load(b, q + 1, false, true);
+            forw_any(a, q);
+            load(a, q + 2, false, true);
+            if (q + 1 < nc) forw_any(b, q + 1);
         }
-        // forward: row swaps and multipliers on x / ||x|| (in place: row k
-        // of the result is written once row k+1 has been read)
-        double carry = Xi[0] * inv;
-        for (int64_t k0 = 0; k0 + 1 < n; k0 += TD_CH) {
-            double nx[TD_CH], lq[TD_CH];
-            unsigned char pq[TD_CH];
-#pragma unroll
-            for (int q = 0; q < TD_CH; ++q) {
-                const int64_t k = k0 + q;
-                nx[q] = lq[q] = 0.0;
-                pq[q] = 0;
-                if (k + 1 < n) {
-                    nx[q] = Xi[(k + 1) * nev] * inv;
-                    lq[q] = Fi[k * s4 + 3 * nev];
-                    pq[q] = Pi[k * nev];
-                }
-            }
-#pragma unroll
-            for (int q = 0; q < TD_CH; ++q) {
-                const int64_t k = k0 + q;
-                if (k + 1 < n) {
-                    if (pq[q]) {
-                        Xi[k * nev] = nx[q];
-                        carry = carry - lq[q] * nx[q];
-                    } else {
-                        Xi[k * nev] = carry;
-                        carry = nx[q] - lq[q] * carry;
-                    }
-                }
-            }
-        }
-        Xi[(n - 1) * nev] = carry;
-        // backward with U
-        double x1 = 0.0, x2 = 0.0;   // solution rows k+1, k+2
-        for (int64_t k0 = n - 1; k0 >= 0; k0 -= TD_CH) {
-            double yq[TD_CH], u0[TD_CH], u1[TD_CH], u2[TD_CH];
-#pragma unroll
-            for (int q = 0; q < TD_CH; ++q) {
-                const int64_t k = k0 - q;
-                yq[q] = u1[q] = u2[q] = 0.0;
-                u0[q] = 1.0;
-                if (k >= 0) {
-                    yq[q] = Xi[k * nev];
-                    u0[q] = Fi[k * s4];
-                    u1[q] = Fi[k * s4 + nev];
-                    u2[q] = Fi[k * s4 + 2 * nev];
-                }
-            }
-#pragma unroll
-            for (int q = 0; q < TD_CH; ++q) {
-                const int64_t k = k0 - q;
-                if (k >= 0) {
-                    const double v = (yq[q] - u1[q] * x1 - u2[q] * x2) / u0[q];
-                    Xi[k * nev] = v;
-                    x2 = x1;
-                    x1 = v;
-                }
-            }
-        }
+        X[(int64_t)(n - 1) * nev] = carry;
     }
+    backward(std::false_type{});
+    sc[i] = sg / sqrt(ss);
 }
 
 // Modified Gram-Schmidt over each cluster of size >= 2 (one workgroup per
@@ -344,23 +477,30 @@ __global__ __launch_bounds__(256) void k_td_ortho(int64_t n, int64_t nev,
     };
     for (int64_t j = i + 1; j < nev && w[j] - w[j - 1] <= thr; ++j) {
         double* __restrict__ zj = Z + j * ldz;
-        for (int64_t m = i; m < j; ++m) {
-            const double* __restrict__ zm = Z + m * ldz;
+        // once, and again where little of the (unit) vector was left: what the
+        // subtractions leave is orthogonal to eps over that little
+        double left = 0.0;
+        for (int pass = 0; pass == 0 || (pass == 1 && left < 1e-4); ++pass) {
+            for (int64_t m = i; m < j; ++m) {
+                const double* __restrict__ zm = Z + m * ldz;
+                double p = 0.0;
+                for (int64_t r = tid; r < n; r += 256) p = fma(zj[r], zm[r], p);
+                const double dt = block_sum(p);
+                for (int64_t r = tid; r < n; r += 256) zj[r] = fma(-dt, zm[r], zj[r]);
+            }
             double p = 0.0;
-            for (int64_t r = tid; r < n; r += 256) p = fma(zj[r], zm[r], p);
-            const double dt = block_sum(p);
-            for (int64_t r = tid; r < n; r += 256) zj[r] = fma(-dt, zm[r], zj[r]);
+            for (int64_t r = tid; r < n; r += 256) p = fma(zj[r], zj[r], p);
+            left = block_sum(p);
         }
-        double p = 0.0;
-        for (int64_t r = tid; r < n; r += 256) p = fma(zj[r], zj[r], p);
-        const double inv = 1.0 / sqrt(block_sum(p));
+        const double inv = 1.0 / sqrt(left);
         for (int64_t r = tid; r < n; r += 256) zj[r] *= inv;
     }
 }
 
-// row-major X (n x nev) -> column-major Z (ldz)
+// row-major X (n x nev) -> column-major Z (ldz), vector c times sc[c]
 __global__ __launch_bounds__(256) void k_td_out(int64_t n, int64_t nev,
                                                 const double* __restrict__ X,
+                                                const double* __restrict__ sc,
                                                 double* __restrict__ Z, int64_t ldz)
 {
     __shared__ double tile[32][33];
@@ -373,7 +513,7 @@ __global__ __launch_bounds__(256) void k_td_out(int64_t n, int64_t nev,
     __syncthreads();
     for (int q = ty; q < 32; q += 8) {
         const int64_t c = c0 + q, r = r0 + tx;
-        if (r < n && c < nev) Z[c * ldz + r] = tile[tx][q];
+        if (r < n && c < nev) Z[c * ldz + r] = tile[tx][q] * sc[c];
     }
 }
 
@@ -435,17 +575,29 @@ int trbt_tridiag_eigh_d(int64_t n, int64_t nev, const double* d, const double* e
     double* e2 = (double*)(ws + L.e2);
     double* bounds = (double*)(ws + L.bounds);
     double* X = (double*)(ws + L.x);
-    double* F = (double*)(ws + L.f);
-    unsigned char* P = (unsigned char*)(ws + L.p);
-    const unsigned nb = (unsigned)((nev + TD_THREADS - 1) / TD_THREADS);
-    const unsigned nbm = (unsigned)((nev * TD_MS + TD_THREADS - 1) / TD_THREADS);
-    hipLaunchKernelGGL(k_td_prep, dim3(1), dim3(256), 0, st, n, d, e, e2, bounds);
-    hipLaunchKernelGGL(k_td_bisect, dim3(nbm), dim3(TD_THREADS), 0, st, n, nev, d,
-                       (const double*)e2, (const double*)bounds, w);
-    hipLaunchKernelGGL(k_td_invit, dim3(nb), dim3(TD_THREADS), 0, st, n, nev, d, e,
-                       (const double*)bounds, (const double*)w, X, F, P);
+    // of the factors' n x nev x 4: V, then 1/e (n) and the vectors' scales (nev)
+    double* V = (double*)(ws + L.f);
+    double* re = V + (size_t)n * nev;
+    double* sc = re + (size_t)n * nev;
+    uint32_t* B = (uint32_t*)(ws + L.p);   // a bit per row and vector, of the n x nev bytes
+    hipLaunchKernelGGL(k_td_prep, dim3(1), dim3(256), 0, st, n, d, e, e2, re, bounds);
+    // lanes per eigenvalue: more lanes need fewer rounds (14, 11, 9 for 16, 32, 64),
+    // and their waves are free while SIMDs stand idle (whole calls, ms: nev =
+    // 400 of 400 0.298, 0.290, 0.274; 2000 of 4000 3.01, 3.00, 3.25; 4096 of
+    // 8192 6.9, 7.4, 8.5; 12000 of 12000 13.9, 15.9, 20.7)
+    auto bisect = [&](auto kern, int ms) {
+        hipLaunchKernelGGL(kern, dim3((unsigned)((nev * ms + TD_THREADS - 1) / TD_THREADS)),
+                           dim3(TD_THREADS), 0, st, n, nev, d, (const double*)e2,
+                           (const double*)bounds, w);
+    };
+    if (nev <= 512) bisect(k_td_bisect<64>, 64);
+    else if (nev <= 2048) bisect(k_td_bisect<32>, 32);
+    else bisect(k_td_bisect<16>, 16);
+    hipLaunchKernelGGL(k_td_invit, dim3((unsigned)((nev + TD_THREADS - 1) / TD_THREADS)),
+                       dim3(TD_THREADS), 0, st, n, nev, d, e, (const double*)re,
+                       (const double*)bounds, (const double*)w, X, V, B, sc);
     hipLaunchKernelGGL(k_td_out, dim3((unsigned)((n + 31) / 32), (unsigned)((nev + 31) / 32)),
-                       dim3(256), 0, st, n, nev, (const double*)X, Z, ldz);
+                       dim3(256), 0, st, n, nev, (const double*)X, (const double*)sc, Z, ldz);
     hipLaunchKernelGGL(k_td_ortho, dim3((unsigned)nev), dim3(256), 0, st, n, nev,
                        (const double*)w, (const double*)bounds, Z, ldz);
     return hipGetLastError() == hipSuccess ? TRBT_SUCCESS : TRBT_ERR_HIP;
