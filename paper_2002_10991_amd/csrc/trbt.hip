@@ -49,23 +49,13 @@ inline int device_cus()
     return cus;
 }
 
-// Launch the blocked forward kernel, with slot groups when the strips alone
-// leave CUs idle and the grid fits on the device at once (a cooperative
-// launch guarantees the workgroups of a strip run concurrently); otherwise
-// one workgroup per strip.
+// Launch the blocked forward kernel on the columns of `strips` strips: with
+// G > 1 slot groups as a cooperative launch (the workgroups of a strip run
+// concurrently), else, or where that is not possible, one workgroup per strip.
 template <int NB, int CT, bool CPLX, int D, int NW, bool ROT>
-int launch_blocked(int64_t n, int64_t nev, const double* ws, double* Z, int64_t ldz,
-                   unsigned* err, int* gprog, hipStream_t st)
+int launch_strips(int64_t n, int64_t nev, const double* ws, double* Z, int64_t ldz,
+                  unsigned* err, int* gprog, int64_t strips, int64_t G, int cus, hipStream_t st)
 {
-    const int64_t strips = (nev + 16 * CT - 1) / (16 * CT);
-    const int64_t rounds = (sweeps_in_stage(n, NB, 0) + NW - 1) / NW;
-    const int cus = device_cus();
-    int64_t G = 1;
-    if (cus > 0 && strips < cus) {
-        G = cus / strips;
-        if (G > rounds) G = rounds;
-        if (G > GMAX) G = GMAX;
-    }
     if (G > 1) {
         auto kern = k_blocked<NB, CT, CPLX, D, NW, ROT, true>;
         const int64_t grid = (strips + 7) / 8 * 8 * G;
@@ -88,6 +78,49 @@ int launch_blocked(int64_t n, int64_t nev, const double* ws, double* Z, int64_t 
                        dim3(64 * NW), 0, st, n, nev, ws, Z, ldz, err, 1, (int*)nullptr);
     return hipGetLastError() == hipSuccess ? TRBT_SUCCESS : TRBT_ERR_HIP;
 }
+
+// The blocked forward: a CU holds one workgroup (registers), so the strips
+// go in passes over the CUs.  Whole passes run without slot groups; the
+// strips left over share the CUs in slot groups (as many per strip as fit:
+// the grid is padded to 8 strips), so that a last pass with few strips takes
+// a fraction of a pass.  More than half the CUs' number of strips leaves no
+// room for two groups each; up to five eighths, half a device of strips in
+// two groups and then the few others in many take less than the one pass.
+// Measured, one launch for all strips -> these passes, nbw = 64, ms: real
+// n = 8192, nev = 5000 22.6 -> 17.7, 6000 22.7 -> 20.0, 2600 13.0 -> 10.9;
+// real n = 3000, nev = 800 (50 strips, whose 5 groups did not fit once
+// padded) 1.57 -> 1.00; complex n = 6000, nev = 4800 38.9 -> 24.8, 2500
+// 18.9 -> 15.8.  At three quarters (real n = 4096, nev = 3000) splitting
+// costs 4%.
+template <int NB, int CT, bool CPLX, int D, int NW, bool ROT>
+int launch_blocked(int64_t n, int64_t nev, const double* ws, double* Z, int64_t ldz,
+                   unsigned* err, int* gprog, hipStream_t st)
+{
+    const int64_t strips = (nev + 16 * CT - 1) / (16 * CT);
+    const int64_t rounds = (sweeps_in_stage(n, NB, 0) + NW - 1) / NW;
+    const int64_t cus = device_cus();
+    for (int64_t s0 = 0; s0 < strips;) {
+        int64_t take = strips - s0, G = 1;
+        if (cus > 0 && rounds > 1) {
+            if (take >= cus) {
+                take = take / cus * cus;
+            } else {
+                if (take > cus / 2 && take <= cus / 8 * 5) take = cus / 2;
+                G = cus / ((take + 7) / 8 * 8);   // the grid is padded to 8 strips
+                G = G > rounds ? rounds : G;
+                G = G > GMAX ? GMAX : G;
+            }
+        }
+        const int64_t c0 = s0 * 16 * CT, c1 = (s0 + take) * 16 * CT;
+        const int rc = launch_strips<NB, CT, CPLX, D, NW, ROT>(
+            n, (c1 < nev ? c1 : nev) - c0, ws, Z + c0 * ldz * (CPLX ? 2 : 1), ldz, err, gprog,
+            take, G, (int)cus, st);
+        if (rc) return rc;
+        s0 += take;
+    }
+    return TRBT_SUCCESS;
+}
+
 template <bool CPLX>
 int prepare(int64_t n, int nbw, const double* hv, const double* ht, void* work,
             size_t work_bytes, void* stream_v)
@@ -145,17 +178,29 @@ int apply(int64_t n, int nbw, int64_t nev, const double* hv, const double* ht, d
         unsigned* err = (unsigned*)work;
         int* gprog = (int*)((char*)work + blocked_bytes(n, nbw, CPLX));
         // nbw > 64: windows of 6..9 tiles need one wave per SIMD (4 waves,
-        // all 512 registers) and a half-block operand ring; real nbw <= 64:
-        // two column tiles per wave
+        // all 512 registers) and a half-block operand ring.
+        // Real nbw <= 64 takes one or two column tiles per wave.  Two halve
+        // the operand reads from the L2 (with one, 256 workgroups read
+        // 13 TB/s and wait for it); one halves the time of a block, and with
+        // it the fill and drain of the slot pipeline.  The line is 12 rounds of
+        // the slots of all 16-column strips over the device's waves.  One tile
+        // against two, us (rounds): n = 1024, nbw 32, all columns 300 : 450
+        // (1); 2048, 64, all 696 : 1049 (2); 3000, 32, all 2316 : 2416 (9);
+        // 4096, 64, all 3416 : 3599 (8); 3000, 16, all 3499 : 3500 (17); 4096,
+        // 32, all 4390 : 4270 (16); 8192, 64, 4096 13220 : 12780 (16); 6144,
+        // 64, all 14900 : 13020 (18); 8192, 32, 2048 12265 : 9283 (16).
+#define TRBT_LAUNCH(NBV, CTV)                                                                  \
+    launch_blocked<NBV, CTV, CPLX,                                                             \
+                   (NBV <= 64 || CPLX) ? ring_depth<NBV, CPLX, CTV>() : 4 * (NBV / 16 + 1),    \
+                   NBV <= 64 ? WAVES : 4, rotating_window<NBV, CPLX>()>(n, nev, ws, Z, ldz,    \
+                                                                        err, gprog, st)
 #define TRBT_MAIN(NBV)                                                                         \
-    case NBV: {                                                                                \
-        constexpr bool ROT = rotating_window<NBV, CPLX>();                                     \
-        constexpr int CTV = (!CPLX && NBV <= 64) ? 2 : 1;                                       \
-        constexpr int NW = NBV <= 64 ? WAVES : 4;                                              \
-        constexpr int D = (NBV <= 64 || CPLX) ? ring_depth<NBV, CPLX, CTV>()                   \
-                                              : 4 * (NBV / 16 + 1);                            \
-        return launch_blocked<NBV, CTV, CPLX, D, NW, ROT>(n, nev, ws, Z, ldz, err, gprog, st); \
-    }
+    case NBV:                                                                                  \
+        if constexpr (!CPLX && NBV <= 64)                                                      \
+            if (two_tiles) return TRBT_LAUNCH(NBV, 2);                                         \
+        return TRBT_LAUNCH(NBV, 1);
+        const bool two_tiles = (nev + 15) / 16 * sweeps_in_stage(n, nbw, 0) >=
+                               (int64_t)12 * WAVES * device_cus();
         switch (nbw) {
             TRBT_MAIN(16)
             TRBT_MAIN(32)
@@ -168,6 +213,7 @@ int apply(int64_t n, int nbw, int64_t nev, const double* hv, const double* ht, d
             default: return TRBT_ERR_INTERNAL;
         }
 #undef TRBT_MAIN
+#undef TRBT_LAUNCH
     } else {
         // the fault word, where the caller gave a workspace
         unsigned* err = work && work_bytes >= sizeof(unsigned) ? (unsigned*)work : nullptr;

@@ -280,9 +280,9 @@ __device__ inline void wy_factor(int64_t n, const double* __restrict__ hv,
 }
 
 // Window form of the blocked kernels: complex windows always rotate; real
-// ones rotate for nbw = 48 and 64, where each wave's two column tiles on a
-// fixed window would spill (the slide needs a second set of tile registers),
-// and stay fixed for nbw <= 32 (fewer instructions per block: 5% faster at
+// ones rotate for nbw = 48 and 64, where two column tiles per wave on a fixed
+// window would spill (the slide needs a second set of tile registers), and
+// stay fixed for nbw <= 32 (fewer instructions per block: 5% faster at
 // n = 1024, nbw = 32) and for the wide bands (one tile per wave).  Every
 // form of the back-transformation (single problem, batched, the adjoint's
 // checkpointing forward) takes the same form for the same nbw, so their
@@ -469,6 +469,49 @@ __device__ inline void load_tile(Tile<CPLX>& t, const double* __restrict__ Z, in
             const double x = Z[cc * ldz + rr];
             t.re[e] = ok ? x : 0.0;
         }
+    }
+}
+
+// The same in two halves: issue_tile issues the loads (from clamped, valid
+// addresses where rows or columns lie outside the matrix), mask_tile zeroes
+// what lies outside, where the tile is used.  (A select right behind the loads
+// would wait for them.)
+template <bool CPLX>
+__device__ inline void issue_tile(Tile<CPLX>& t, const double* __restrict__ Z, int64_t ldz,
+                                 int64_t n, int64_t nev, int64_t row0, int64_t col,
+                                 bool coh = false)
+{
+    const int64_t cc = col < nev ? col : nev - 1;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+        const int64_t r = row0 + 4 * e;
+        const int64_t rr = r < 0 ? 0 : (r >= n ? n - 1 : r);
+        if (coh) {
+            if constexpr (CPLX) {
+                t.re[e] = ld_coh(Z + 2 * (cc * ldz + rr));
+                t.im[e] = ld_coh(Z + 2 * (cc * ldz + rr) + 1);
+            } else {
+                t.re[e] = ld_coh(Z + cc * ldz + rr);
+            }
+        } else if constexpr (CPLX) {
+            const d2 x = *(const d2*)(Z + 2 * (cc * ldz + rr));
+            t.re[e] = x[0];
+            t.im[e] = x[1];
+        } else {
+            t.re[e] = Z[cc * ldz + rr];
+        }
+    }
+}
+
+template <bool CPLX>
+__device__ inline void mask_tile(Tile<CPLX>& t, int64_t n, int64_t nev, int64_t row0, int64_t col)
+{
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+        const int64_t r = row0 + 4 * e;
+        const bool ok = col < nev && r >= 0 && r < n;
+        t.re[e] = ok ? t.re[e] : 0.0;
+        if constexpr (CPLX) t.im[e] = ok ? t.im[e] : 0.0;
     }
 }
 
@@ -792,6 +835,16 @@ __device__ __attribute__((always_inline)) inline void blocked_strip(int64_t n, i
                            : wait_counter(prog, wprev, need, err, lane, seen_prog);
     };
 
+    // a window tile from Z; a real one that crosses the matrix's edge is
+    // masked later, by its user (complex blocks have no registers for that:
+    // 2% slower at n = 1500, nbw = 32)
+    auto fetch = [&](Tile<CPLX>& x, int64_t row0, int64_t col, bool inside) {
+        if constexpr (CPLX)
+            load_tile<CPLX>(x, Z, ldz, n, nev, row0, col, inside, pred_global);
+        else
+            issue_tile<CPLX>(x, Z, ldz, n, nev, row0, col, pred_global);
+    };
+
     for (int64_t j = (int64_t)grp * NW + w; j < J; j += (int64_t)NW * ngroups) {
         const int64_t t0 = j * nt1;
         // the slot's operand stream; blocks are PB doubles apart
@@ -808,11 +861,17 @@ __device__ __attribute__((always_inline)) inline void blocked_strip(int64_t n, i
             const bool inside = cols_inside && p0 + 16 * q >= 0 && p0 + 16 * q + 16 <= n;
 #pragma unroll
             for (int c = 0; c < CT; ++c)
-                load_tile<CPLX>(zt[q][c], Z, ldz, n, nev, p0 + 16 * q + rsub,
-                                col_base + 16 * c, inside, pred_global);
+                fetch(zt[q][c], p0 + 16 * q + rsub, col_base + 16 * c, inside);
         }
 #pragma unroll
         for (int c = 0; c < D; ++c) load_chunk<CPLX, D>(ops, 0, c, lane, ring_re, ring_im, c);
+        if (!CPLX && !(cols_inside && p0 >= 0 && p0 + 16 * NT <= n)) {
+#pragma unroll
+            for (int q = 0; q < NT; ++q)
+#pragma unroll
+                for (int c = 0; c < CT; ++c)
+                    mask_tile<CPLX>(zt[q][c], n, nev, p0 + 16 * q + rsub, col_base + 16 * c);
+        }
 
         int rot = 0;   // register tile of the window's top tile (wave-uniform)
         for (int64_t t = t0; t < nblk; ++t, boff += G::PB * sizeof(double), p0 -= KB) {
@@ -833,22 +892,27 @@ __device__ __attribute__((always_inline)) inline void blocked_strip(int64_t n, i
                 const bool inside = cols_inside && p0 - 16 >= 0 && p0 <= n;
 #pragma unroll
                 for (int c = 0; c < CT; ++c)
-                    load_tile<CPLX>(znext[c], Z, ldz, n, nev, p0 - 16 + rsub, col_base + 16 * c,
-                                    inside, pred_global);
+                    fetch(znext[c], p0 - 16 + rsub, col_base + 16 * c, inside);
             }
+            const bool zedge =
+                !CPLX && !xin && has_next && !(cols_inside && p0 - 16 >= 0 && p0 <= n);
 
-            // operand chunk c of this block sits in ring slot c % D; as soon
-            // as it has been read the slot is refilled with chunk c + D
-            // (running into the next block).  (Refilling only after the
-            // chunk's MFMAs saves register copies but makes the load wait for
-            // the MFMA to read its operand: slower.)
+            // operand chunk c of this block sits in ring slot c % D; behind
+            // its last product the slot is refilled with chunk c + D (running
+            // into the next block).  No branch around the loads, and their
+            // place among the products pinned: with either left to the
+            // compiler it copied ring registers between blocks and waited for
+            // all loads in flight at a block's first product (n = 1024, nbw = 32,
+            // two column tiles per wave: 508 us instead of 450).  The slot's
+            // last block reads its own chunks again.
+            const uint32_t bnext = boff + (has_next ? (uint32_t)(G::PB * sizeof(double)) : 0u);
             auto refill = [&](int c) {
                 const int slot = c % D;
                 if (c + D < NCH)
                     load_chunk<CPLX, D>(ops, boff, c + D, lane, ring_re, ring_im, slot);
-                else if (has_next)
-                    load_chunk<CPLX, D>(ops, boff + G::PB * sizeof(double), c + D - NCH, lane,
-                                        ring_re, ring_im, slot);
+                else
+                    load_chunk<CPLX, D>(ops, bnext, c + D - NCH, lane, ring_re, ring_im, slot);
+                __builtin_amdgcn_sched_barrier(0);
             };
             bool xfail = false;
             Tile<CPLX> zsh[ROT ? 1 : NT + 1][CT];   // fixed window: the window after the slide
@@ -881,7 +945,7 @@ __device__ __attribute__((always_inline)) inline void blocked_strip(int64_t n, i
             };
 
             if constexpr (ROT && !CPLX) {
-                // Real, rotating window (two column tiles): GEMM1 by
+                // Real, rotating window: GEMM1 by
                 // register tile, then GEMM2 register tiles from NT-1 down,
                 // u ascending; each operand chunk feeds CT MFMAs.
                 Tile<CPLX> y[2][CT];
@@ -892,11 +956,11 @@ __device__ __attribute__((always_inline)) inline void blocked_strip(int64_t n, i
 #pragma unroll
                 for (int c = 0; c < 4 * NT; ++c) {
                     const double ar = ring_re[c % D];
-                    refill(c);
                     const int h = c / 4, u = c % 4;
 #pragma unroll
                     for (int cc = 0; cc < CT; ++cc)
                         y[h & 1][cc].re = mfma_n<0>(ar, zt[h][cc].re[u], y[h & 1][cc].re);
+                    refill(c);
                 }
 #pragma unroll
                 for (int cc = 0; cc < CT; ++cc) y[0][cc].re += y[1][cc].re;
@@ -918,11 +982,11 @@ __device__ __attribute__((always_inline)) inline void blocked_strip(int64_t n, i
                 for (int c2 = 0; c2 < 4 * NT; ++c2) {
                     const int c = 4 * NT + c2;
                     const double ar = ring_re[c % D];
-                    refill(c);
                     const int h = NT - 1 - c2 / 4, u = c2 % 4;
 #pragma unroll
                     for (int cc = 0; cc < CT; ++cc)
                         zt[h][cc].re = mfma_n<0>(ar, y[0][cc].re[u], zt[h][cc].re);
+                    refill(c);
                 }
             } else if constexpr (CPLX) {
                 // Complex products with three real MFMAs each.
@@ -934,7 +998,6 @@ __device__ __attribute__((always_inline)) inline void blocked_strip(int64_t n, i
 #pragma unroll
                 for (int c = 0; c < 4 * NT; ++c) {
                     const double ar = ring_re[c % D], ai = ring_im[c % D];
-                    refill(c);
                     const double as = ar + ai;
                     const int h = c / 4, u = c % 4;
 #pragma unroll
@@ -944,6 +1007,7 @@ __device__ __attribute__((always_inline)) inline void blocked_strip(int64_t n, i
                         yb[cc] = mfma_n<0>(ai, zi, yb[cc]);
                         yc[cc] = mfma_n<0>(as, zr + zi, yc[cc]);
                     }
+                    refill(c);
                 }
                 if constexpr (CKPT) {
                     // the block's input window: GEMM1 has only read it and
@@ -981,7 +1045,6 @@ __device__ __attribute__((always_inline)) inline void blocked_strip(int64_t n, i
                 for (int c2 = 0; c2 < 4 * NT; ++c2) {
                     const int c = 4 * NT + c2;
                     const double ar = ring_re[c % D], ai = ring_im[c % D];
-                    refill(c);
                     const double as = ar + ai;
                     const int h = NT - 1 - c2 / 4, u = c2 % 4;
 #pragma unroll
@@ -994,6 +1057,7 @@ __device__ __attribute__((always_inline)) inline void blocked_strip(int64_t n, i
                             zt[h][cc].im += kk[cc];
                         }
                     }
+                    refill(c);
                 }
             } else {
                 Tile<CPLX> y[2][CT];   // two partial sums: more independent MFMA chains
@@ -1004,7 +1068,6 @@ __device__ __attribute__((always_inline)) inline void blocked_strip(int64_t n, i
 #pragma unroll
                 for (int c = 0; c < NCH; ++c) {
                     const double ar = ring_re[c % D];
-                    refill(c);
                     if constexpr (CKPT) {
                         // the block's input window: GEMM1 has only read it and
                         // GEMM2 is about to overwrite it (storing here rather
@@ -1041,11 +1104,17 @@ __device__ __attribute__((always_inline)) inline void blocked_strip(int64_t n, i
                             Tile<CPLX>& dst = (u == 3) ? zsh[q + 1][cc] : zt[q][cc];
                             dst.re = mfma_n<0>(ar, y[0][cc].re[u], src.re);
                         }
-                        if (u == 3 && q == NT - 1) store_bottom(zsh[NT]);
                     }
+                    refill(c);
+                    if (c == NCH - NT) store_bottom(zsh[NT]);   // its last product is done
                 }
             }
 
+            if (zedge) {
+#pragma unroll
+                for (int c = 0; c < CT; ++c)
+                    mask_tile<CPLX>(znext[c], n, nev, p0 - 16 + rsub, col_base + 16 * c);
+            }
             if constexpr (ROT) {
                 // the bottom tile is final: hand it off; its registers take
                 // the next block's top tile
