@@ -154,35 +154,41 @@ __device__ inline void stx_coh(double* p, cx v)
     if constexpr (C) __hip_atomic_store(p + 1, v.im, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
-template <bool C>
-__device__ inline cx shfl_x(cx v, int src)
+// One level of a sum over the lanes that leaves each lane one of two values:
+// v0 where `second` is clear, v1 where it is set, plus the same of the lane
+// that CTRL moves here (whose `second` is the other)
+template <int CTRL>
+__device__ inline double halve(double v0, double v1, bool second)
 {
-    cx r;
-    r.re = __shfl(v.re, src, 64);
-    r.im = C ? __shfl(v.im, src, 64) : 0.0;
-    return r;
+    const double keep = second ? v1 : v0, send = second ? v0 : v1;
+    return keep + dpp_f64<CTRL>(send);
 }
 
-// sums over the 64 lanes of N values at once (every lane gets every sum):
-// within rows by DPP, then across the four rows by two lane swaps; the N
-// values are independent and interleave
-template <bool C, int N>
-__device__ inline void wave_sums(cx (&v)[N])
+// Sums over the 64 lanes of 4 values, given with the pairs of lanes added (the
+// two lanes of a pair may differ: a pair's sum is one product rounded and one
+// fused, whichever is the lane's own).  The additions are wave_sum's; but
+// from the quads on a lane carries two values, and from the half rows on one,
+// so that the four sums take 17 additions for the 24 of four wave_sums and
+// 60% of the instructions.  Which of the two forms of a pair a sum takes
+// per quad depends on the lane: lane = quad in one parity, the other in
+// the other; every lane fetches the four sums of its own kind.
+__device__ inline void wave_sums4(double (&v)[4], int lane)
 {
+    const bool k = (lane ^ (lane >> 1)) & 1;          // lanes 0, 3 of a quad: values 0, 1
+    const double a = halve<0x4E>(v[0], v[2], k), b = halve<0x4E>(v[1], v[3], k);
+    double x = halve<0x141>(a, b, lane & 4);          // half rows: quads 0 + 1, 2 + 3
+    x += dpp_f64<0x108>(x);                           // rows (right in their first half)
+    x = swap_add<32>(swap_add<16>(x));
+    // lane 0 .. 7 of a row: values 0, 2, 2, 0, 1, 3, 3, 1 of kind 0, 1, 0, 1, 1, 0, 1, 0
+    const bool odd = (lane ^ (lane >> 2)) & 1;
+    const uint64_t u = __builtin_bit_cast(uint64_t, x);
 #pragma unroll
-    for (int t = 0; t < N; ++t) {
-        v[t].re = row_sum(v[t].re);
-        if constexpr (C) v[t].im = row_sum(v[t].im);
-    }
-#pragma unroll
-    for (int t = 0; t < N; ++t) {
-        v[t].re = swap_add<16>(v[t].re);
-        if constexpr (C) v[t].im = swap_add<16>(v[t].im);
-    }
-#pragma unroll
-    for (int t = 0; t < N; ++t) {
-        v[t].re = swap_add<32>(v[t].re);
-        if constexpr (C) v[t].im = swap_add<32>(v[t].im);
+    for (int t = 0; t < 4; ++t) {
+        constexpr int from[4][2] = {{0, 3}, {7, 4}, {2, 1}, {5, 6}};
+        const int src = 4 * (odd ? from[t][1] : from[t][0]);
+        const uint32_t lo = (uint32_t)__builtin_amdgcn_ds_bpermute(src, (int)(uint32_t)u);
+        const uint32_t hi = (uint32_t)__builtin_amdgcn_ds_bpermute(src, (int)(uint32_t)(u >> 32));
+        v[t] = __builtin_bit_cast(double, ((uint64_t)hi << 32) | lo);
     }
 }
 
@@ -242,10 +248,14 @@ __global__ __launch_bounds__(64 * NW) void k_chase(int64_t n, int b,
     const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
 
     __shared__ double As[CH_BMAX * CH_PITCH * E];   // diagonal block, column-major, dense
-    __shared__ double vs[CH_BMAX * E];
+    // the reflector, in turn for even and odd steps: a step's tail still
+    // reads it while wave 0 builds the next one
+    __shared__ double vs2[2][CH_BMAX * E];
     constexpr int COLS = CH_BMAX / NW;   // block columns per wave
     __shared__ double zs[NW][CH_BMAX * E], ps[NW][CH_BMAX * E];
-    __shared__ double tau_s[2];
+    __shared__ double zsum[CH_BMAX * E], wvs[CH_BMAX * E];
+    __shared__ double tau_s[3];   // tau and beta
+    static_assert(COLS == 4, "wave_sums4");
     __shared__ int64_t s_sh;
     __shared__ int fail_sh;
     // tail waits of this workgroup that wave 0 has seen end (the other
@@ -254,8 +264,15 @@ __global__ __launch_bounds__(64 * NW) void k_chase(int64_t n, int b,
     // `tick`), so a wave that reads it late still finds a value at least
     // its own count.
     __shared__ int64_t seen_sh;
-    if (threadIdx.x == 0) seen_sh = 0;
+    // waves whose stores of a step have completed, over all steps published
+    // ahead of their tail
+    __shared__ unsigned drained;
+    if (threadIdx.x == 0) {
+        seen_sh = 0;
+        drained = 0;
+    }
     int64_t tick = 0;
+    unsigned early = 0;
 
     auto at = [&](int64_t i, int64_t k) { return bd + ((i - k) + k * LD) * E; };
     // the same address as column base + row offset: B(i, k) is at
@@ -282,16 +299,47 @@ __global__ __launch_bounds__(64 * NW) void k_chase(int64_t n, int b,
         // block), and no other step touches it in between (the one shared
         // entry, its last, was finished in the previous step's tail)
         cx car[COLS];
-        for (int j = 0; j < S; ++j, ++kref) {
-            // (s-1, 0 .. j+1) done: for j > 0 the previous step's tail already
-            // waited for that
-            if (s > 0 && j == 0) {
-                if (threadIdx.x == 0) {
-                    fail_sh = !chase_wait(&prog[s - 1], j + 2 < Sp ? j + 2 : Sp, ctl);
-                }
-                __syncthreads();
-                if (fail_sh) return;
+        // loads of step j's right and diagonal blocks.  Every lane issues
+        // every load (from a valid dummy address where it has no entry), so
+        // the loads of all columns are in flight together instead of one
+        // masked load and its wait at a time.  The corner is read in the
+        // tail: step (s-1, j+2) may be writing it now.
+        cx yr[COLS], ad[COLS];
+        auto load_blocks = [&](int j) {
+            const int r0 = s + 1 + j * b;
+            const int len = nn - r0 < b ? nn - r0 : b;
+            const int rest = nn - r0 - len;
+            const int nr = rest < b ? rest : b;
+            const bool crow = len == b && nr == b && lane == b - 1;
+            double* const cw = bd + (int64_t)(r0 + w) * CS;
+            const int64_t rd = (int64_t)(r0 + lane) * E, rr = (int64_t)(r0 + len + lane) * E;
+#pragma unroll
+            for (int t = 0; t < COLS; ++t) {
+                const int m = w + NW * t;
+                const bool okr = m < len && lane < nr && !(crow && m == b - 1);
+                const bool okd = m < len && lane >= m && lane < len;
+                yr[t] = ldx_coh<C>(okr ? cw + t * SNW + rr : bd);
+                ad[t] = ldx_coh<C>(okd ? cw + t * SNW + rd : bd);
             }
+        };
+        // publish step j: every wave waits until its (device-coherent)
+        // stores have completed, the workgroup meets, and one counter
+        // store.  A waiting stage reads the counter, then the band with
+        // device-coherent loads, so it sees every store made before the
+        // counter.  (Agent-scope release and acquire fences would write
+        // back and invalidate the whole L2 of the XCD at every step; one
+        // atomic add per wave instead of the barrier was much slower:
+        // the adds to one address serialise.)
+        // (s-1, 0 .. 1) done: a later step's start is covered by the tail of
+        // the step before
+        if (s > 0) {
+            if (threadIdx.x == 0) fail_sh = !chase_wait(&prog[s - 1], 2 < Sp ? 2 : Sp, ctl);
+            __syncthreads();
+            if (fail_sh) return;
+        }
+        load_blocks(0);
+        for (int j = 0; j < S; ++j, ++kref) {
+            double* const vs = vs2[j & 1];
             const int r0 = s + 1 + j * b;
             const int len = nn - r0 < b ? nn - r0 : b;
             const int rest = nn - r0 - len;
@@ -316,20 +364,23 @@ __global__ __launch_bounds__(64 * NW) void k_chase(int64_t n, int b,
                 if (j > 0) x = car[0];
                 else if (lane < len) x = ldx_coh<C>(bd + (int64_t)c * CS + rd);
             }
-            cx yl[COLS], yr[COLS], ad[COLS];
-            // every lane issues every load (from a valid dummy address where
-            // it has no entry), so the loads of all columns are in flight
-            // together instead of one masked load and its wait at a time
+            cx yl[COLS];
+#pragma unroll
+            for (int t = 0; t < COLS; ++t)
+                yl[t] = (j > 0 && w + NW * t >= 1) ? car[t] : cx{0.0, 0.0};
+            // the mirror of the diagonal block (its loads were issued in the
+            // previous step's tail)
 #pragma unroll
             for (int t = 0; t < COLS; ++t) {
                 const int m = w + NW * t;
-                yl[t] = (j > 0 && m >= 1) ? car[t] : cx{0.0, 0.0};
-                // (the corner is read in the tail: step (s-1, j+2) may be
-                // writing it now)
                 const bool okr = m < len && lane < nr && !(crow && m == b - 1);
                 const bool okd = m < len && lane >= m && lane < len;
-                yr[t] = ldx_coh<C>(okr ? cw + t * SNW + rr : bd);
-                ad[t] = ldx_coh<C>(okd ? cw + t * SNW + rd : bd);
+                if (!okr) yr[t] = cx{0.0, 0.0};
+                if (!okd) ad[t] = cx{0.0, 0.0};
+                if (okd) {
+                    stx<C>(&As[(m * CH_PITCH + lane) * E], ad[t]);
+                    if (lane > m) stx<C>(&As[(lane * CH_PITCH + m) * E], cx{ad[t].re, -ad[t].im});
+                }
             }
             // 2. the reflector (wave 0)
             if (w == 0) {
@@ -361,46 +412,16 @@ __global__ __launch_bounds__(64 * NW) void k_chase(int64_t n, int b,
                 if (lane == 0) {
                     tau_s[0] = tau.re;
                     tau_s[1] = tau.im;
-                    stx<C>(ht + kref * E, tau);
-                }
-                if (lane < b) stx<C>(hv + (kref * b + lane) * E, v);
-                if (lane < len) stx_coh<C>(bd + (int64_t)c * CS + rd, lane == 0 ? cx{beta, 0.0} : cx{0.0, 0.0});
-            }
-            // the mirror of the diagonal block (its loads have been in flight
-            // while wave 0 built the reflector)
-#pragma unroll
-            for (int t = 0; t < COLS; ++t) {
-                const int m = w + NW * t;
-                const bool okr = m < len && lane < nr && !(crow && m == b - 1);
-                const bool okd = m < len && lane >= m && lane < len;
-                if (!okr) yr[t] = cx{0.0, 0.0};
-                if (!okd) ad[t] = cx{0.0, 0.0};
-                if (okd) {
-                    stx<C>(&As[(m * CH_PITCH + lane) * E], ad[t]);
-                    if (lane > m) stx<C>(&As[(lane * CH_PITCH + m) * E], cx{ad[t].re, -ad[t].im});
+                    tau_s[2] = beta;
                 }
             }
-
             __syncthreads();
 
-            // 3. left block; partial products of the right and diagonal blocks
+            // 3. partial products of the right and diagonal blocks; the
+            // reflector and the annihilated column stored by other waves
+            // than the one that built it
             const cx vi = ldx<C>(&vs[lane * E]);
             const cx tau = {tau_s[0], C ? tau_s[1] : 0.0};
-            {
-                cx dot[COLS];
-#pragma unroll
-                for (int t = 0; t < COLS; ++t) dot[t] = cmulc<C>(vi, yl[t]);
-                wave_sums<C, COLS>(dot);
-#pragma unroll
-                for (int t = 0; t < COLS; ++t) {
-                    const int m = w + NW * t;
-                    if (j > 0 && m >= 1 && m < b) {
-                        const cx f = cmulc<C>(tau, dot[t]);           // conj(tau) (v^H y)
-                        yl[t] = csub<C>(yl[t], cmul<C>(f, vi));
-                        if (lane < len) stx_coh<C>(cl + t * SNW + rd, yl[t]);
-                    }
-                }
-            }
             cx zp = {0.0, 0.0}, pp = {0.0, 0.0};
 #pragma unroll
             for (int t = 0; t < COLS; ++t) {
@@ -413,19 +434,61 @@ __global__ __launch_bounds__(64 * NW) void k_chase(int64_t n, int b,
             }
             stx<C>(&zs[w][lane * E], zp);
             stx<C>(&ps[w][lane * E], pp);
+            const double beta = tau_s[2];
             __syncthreads();
 
-            // 4. right and diagonal blocks
-            cx z = ldx<C>(&zs[0][lane * E]), p = ldx<C>(&ps[0][lane * E]);
+            // 4. z and p summed over the waves, by one wave each, while the
+            // others update the left block
+            if (w < 2) {
+                const double* const part = w == 0 ? &ps[0][0] : &zs[0][0];
+                cx x = ldx<C>(part + lane * E);
 #pragma unroll
-            for (int q = 1; q < NW; ++q) {
-                z = cadd<C>(z, ldx<C>(&zs[q][lane * E]));
-                p = cadd<C>(p, ldx<C>(&ps[q][lane * E]));
+                for (int q = 1; q < NW; ++q) x = cadd<C>(x, ldx<C>(part + (q * CH_BMAX + lane) * E));
+                if (w == 0) {
+                    const double sc = wave_sum1(cmulc<C>(vi, x).re);              // v^H A v (real)
+                    const double h = 0.5 * (tau.re * tau.re + tau.im * tau.im) * sc;
+                    const cx tp = cmul<C>(tau, x);
+                    stx<C>(&wvs[lane * E], cx{tp.re - h * vi.re, C ? tp.im - h * vi.im : 0.0});
+                } else {
+                    stx<C>(&zsum[lane * E], x);
+                }
+            } else if (w == 2) {
+                if (lane == 0) stx<C>(ht + kref * E, tau);
+                if (lane < b) stx<C>(hv + (kref * b + lane) * E, vi);
+            } else if (w == 3) {
+                if (lane < len)
+                    stx_coh<C>(bd + (int64_t)c * CS + rd, lane == 0 ? cx{beta, 0.0} : cx{0.0, 0.0});
             }
-            const double sc = wave_sum1(cmulc<C>(vi, p).re);              // v^H A v (real)
-            const double h = 0.5 * (tau.re * tau.re + tau.im * tau.im) * sc;
-            const cx tp = cmul<C>(tau, p);
-            const cx wv = {tp.re - h * vi.re, C ? tp.im - h * vi.im : 0.0};
+            if (j > 0) {
+                // v^H y of the wave's columns
+                double dr[COLS], di[COLS];
+#pragma unroll
+                for (int t = 0; t < COLS; ++t) {
+                    if constexpr (C) {
+                        const cx d = cmulc<C>(vi, yl[t]);
+                        dr[t] = d.re + dpp_f64<0xB1>(d.re);
+                        di[t] = d.im + dpp_f64<0xB1>(d.im);
+                    } else {
+                        dr[t] = __builtin_fma(vi.re, yl[t].re, dpp_f64<0xB1>(vi.re * yl[t].re));
+                        di[t] = 0.0;
+                    }
+                }
+                wave_sums4(dr, lane);
+                if constexpr (C) wave_sums4(di, lane);
+#pragma unroll
+                for (int t = 0; t < COLS; ++t) {
+                    const int m = w + NW * t;
+                    if (m >= 1 && m < b) {
+                        const cx f = cmulc<C>(tau, cx{dr[t], di[t]});   // conj(tau) (v^H y)
+                        yl[t] = csub<C>(yl[t], cmul<C>(f, vi));
+                        if (lane < len) stx_coh<C>(cl + t * SNW + rd, yl[t]);
+                    }
+                }
+            }
+            __syncthreads();
+
+            // 5. right and diagonal blocks
+            const cx z = ldx<C>(&zsum[lane * E]), wv = ldx<C>(&wvs[lane * E]);
             const cx tz = cmul<C>(tau, z);
 #pragma unroll
             for (int t = 0; t < COLS; ++t) {
@@ -436,9 +499,33 @@ __global__ __launch_bounds__(64 * NW) void k_chase(int64_t n, int b,
                         yr[t] = csub<C>(yr[t], cmul_cb<C>(tz, vm));
                         if (!has_next && lane < nr) stx_coh<C>(cw + t * SNW + rr, yr[t]);
                     }
-                    const cx wm = shfl_x<C>(wv, m);
+                    const cx wm = ldx<C>(&wvs[m * E]);
                     ad[t] = csub<C>(ad[t], cadd<C>(cmul_cb<C>(wv, vm), cmul_cb<C>(vi, wm)));
                     if (lane >= m && lane < len) stx_coh<C>(cw + t * SNW + rd, ad[t]);
+                }
+            }
+
+            // the tail's counter, read while the stores complete
+            int ahead = 0;
+            if (s > 0 && w == 0)
+                ahead = __hip_atomic_load(&prog[s - 1], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+
+            // publish ahead of the tail (which stores nothing, unless this is
+            // the stage's last step): the last wave waits until every wave's
+            // stores have completed
+            if (has_next) {
+                asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+                if (lane == 0)
+                    __hip_atomic_fetch_add(&drained, 1u, __ATOMIC_RELEASE,
+                                           __HIP_MEMORY_SCOPE_WORKGROUP);
+                early += NW;
+                if (w == NW - 1) {
+                    while ((int)(__hip_atomic_load(&drained, __ATOMIC_ACQUIRE,
+                                                   __HIP_MEMORY_SCOPE_WORKGROUP) - early) < 0) {
+                    }
+                    if (lane == 0)
+                        __hip_atomic_store(&prog[s], j + 1, __ATOMIC_RELAXED,
+                                           __HIP_MEMORY_SCOPE_AGENT);
                 }
             }
 
@@ -456,7 +543,7 @@ __global__ __launch_bounds__(64 * NW) void k_chase(int64_t n, int b,
                 ++tick;
                 if (w == 0) {
                     if (lane == 0) {
-                        const bool ok = chase_wait(&prog[s - 1], need, ctl);
+                        const bool ok = ahead >= need || chase_wait(&prog[s - 1], need, ctl);
                         __hip_atomic_store(&seen_sh, ok ? tick : INT64_MAX, __ATOMIC_RELEASE,
                                            __HIP_MEMORY_SCOPE_WORKGROUP);
                     }
@@ -476,16 +563,21 @@ __global__ __launch_bounds__(64 * NW) void k_chase(int64_t n, int b,
                     }
                 }
             }
+            asm volatile("" ::: "memory");   // no load below moves above the wait
+            cx cv = {0.0, 0.0};
+            if (crow) cv = ldx_coh<C>(at(r0 + 2 * (int64_t)b - 1, r0 + b - 1));
+#pragma unroll
+            for (int t = 0; t < COLS; ++t) car[t] = yr[t];
+            if (has_next) load_blocks(j + 1);   // in flight from here on
             if (corner) {
                 const cx vb = ldx<C>(&vs[(b - 1) * E]);
                 cx zc = z;
                 if (crow) {
-                    const cx cv = ldx_coh<C>(at(r0 + 2 * (int64_t)b - 1, r0 + b - 1));
                     zc = cadd<C>(z, cmul<C>(cv, vb));
 #pragma unroll
                     for (int t = 0; t < COLS; ++t) {
                         const int m = w + NW * t;
-                        if (m == b - 1) yr[t] = cv;
+                        if (m == b - 1) car[t] = cv;
                     }
                 }
                 const cx tzc = cmul<C>(tau, zc);
@@ -493,26 +585,17 @@ __global__ __launch_bounds__(64 * NW) void k_chase(int64_t n, int b,
                 for (int t = 0; t < COLS; ++t) {
                     const int m = w + NW * t;
                     if (m < len && crow) {
-                        yr[t] = csub<C>(yr[t], cmul_cb<C>(tzc, ldx<C>(&vs[m * E])));
-                        if (!has_next) stx_coh<C>(cw + t * SNW + rr, yr[t]);
+                        car[t] = csub<C>(car[t], cmul_cb<C>(tzc, ldx<C>(&vs[m * E])));
+                        if (!has_next) stx_coh<C>(cw + t * SNW + rr, car[t]);
                     }
                 }
             }
-#pragma unroll
-            for (int t = 0; t < COLS; ++t) car[t] = yr[t];
-
-            // publish the step: every wave waits until its (device-coherent)
-            // stores have completed, the workgroup meets, and one counter
-            // store.  A waiting stage reads the counter, then the band with
-            // device-coherent loads, so it sees every store made before the
-            // counter.  (Agent-scope release and acquire fences would write
-            // back and invalidate the whole L2 of the XCD at every step; one
-            // atomic add per wave instead of the barrier was much slower:
-            // the adds to one address serialise.)
-            asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-            __syncthreads();
-            if (threadIdx.x == 0)
-                __hip_atomic_store(&prog[s], (int)(j + 1), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            if (!has_next) {
+                asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+                __syncthreads();
+                if (threadIdx.x == 0)
+                    __hip_atomic_store(&prog[s], j + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            }
         }
     }
 }
