@@ -46,19 +46,36 @@
 // One step on one workgroup of 16 waves, lane = row of the block, block
 // columns dealt round-robin over the waves by their offset (from c for the
 // left block, from r0 for the others):
-//   1. all waves load their columns of the right and diagonal blocks (the
-//      left block and column c come from the registers of the previous
-//      step, or column c from memory for j = 0); the diagonal block is also
-//      mirrored into LDS as a dense Hermitian matrix;
-//   2. wave 0 builds the reflector (one wave-wide sum of squares), writes
-//      (v, tau) and the annihilated column;
-//   3. left block: y <- y - conj(tau) v (v^H y) per column (wave-wide sums,
-//      all of a wave's columns reduced together); right block: partial
-//      products z = M v; diagonal block: partial products p = A v;
-//   4. z and p summed over the waves in fixed order; w = tau p -
-//      (|tau|^2/2)(v^H p) v; right block M <- M - tau z v^H; diagonal block
-//      A <- A - w v^H - v w^H (the two-sided product written as a rank-2
-//      update, which is H^H A H expanded), lower triangle stored.
+//   1. the diagonal block is mirrored into LDS as a dense Hermitian matrix;
+//      its and the right block's columns were loaded in the previous step's
+//      tail (the left block and column c are the previous step's right
+//      block, or column c comes from memory for j = 0);
+//   2. wave 0 builds the reflector (one wave-wide sum of squares);
+//   3. right block: partial products z = M v; diagonal block: partial
+//      products p = A v, per wave;
+//   4. wave 0 sums p over the waves in fixed order and makes w = tau p -
+//      (|tau|^2/2)(v^H p) v, wave 1 sums z; meanwhile the others update the
+//      left block, y <- y - conj(tau) v (v^H y) per column (a wave's four
+//      inner products summed over the lanes together), and store (v, tau)
+//      and the annihilated column;
+//   5. right block M <- M - tau z v^H; diagonal block A <- A - w v^H - v w^H
+//      (the two-sided product written as a rank-2 update, which is H^H A H
+//      expanded), lower triangle stored;
+//   6. the step is published as soon as these stores have completed, the
+//      tail waits for (s-1, j+2), and the next step's loads are issued with
+//      the corner's.
+// Publishing ahead of the tail is sound because the tail of a step with a
+// successor stores nothing (the right block stays in registers), and the
+// tail's own wait covers the loads of (s, j+1): every conflicting pair of
+// loads, body and tail is ordered as in the sequential order, checked
+// exhaustively over b = 2 .. 8 and ragged n <= 70, and with one step less
+// anywhere it is not.
+//
+// What bounds it: the chain of 2n steps, each as long as the work and the
+// waits of one workgroup (a CU's instruction issue in 3 to 5, device-coherent
+// round trips of 0.8 us in 6).  n = 8192, nbw = 64, real: 6.4 -> 5.1 us a step
+// (reflector 0.7, products 0.7, sums and left block 1.0, updates and their
+// stores 0.9, tail 1.3, barriers and waits the rest), 106.5 -> 85 ms.
 
 #include <hip/hip_runtime.h>
 
@@ -180,12 +197,11 @@ __device__ inline void wave_sums4(double (&v)[4], int lane)
     x += dpp_f64<0x108>(x);                           // rows (right in their first half)
     x = swap_add<32>(swap_add<16>(x));
     // lane 0 .. 7 of a row: values 0, 2, 2, 0, 1, 3, 3, 1 of kind 0, 1, 0, 1, 1, 0, 1, 0
-    const bool odd = (lane ^ (lane >> 2)) & 1;
+    const int odd = (lane ^ (lane >> 2)) & 1 ? 12 : 0;
     const uint64_t u = __builtin_bit_cast(uint64_t, x);
 #pragma unroll
     for (int t = 0; t < 4; ++t) {
-        constexpr int from[4][2] = {{0, 3}, {7, 4}, {2, 1}, {5, 6}};
-        const int src = 4 * (odd ? from[t][1] : from[t][0]);
+        const int src = (t == 0 ? 0 : t == 1 ? 28 : t == 2 ? 8 : 20) ^ odd;   // 4 lane
         const uint32_t lo = (uint32_t)__builtin_amdgcn_ds_bpermute(src, (int)(uint32_t)u);
         const uint32_t hi = (uint32_t)__builtin_amdgcn_ds_bpermute(src, (int)(uint32_t)(u >> 32));
         v[t] = __builtin_bit_cast(double, ((uint64_t)hi << 32) | lo);
@@ -568,7 +584,10 @@ __global__ __launch_bounds__(64 * NW) void k_chase(int64_t n, int b,
             if (crow) cv = ldx_coh<C>(at(r0 + 2 * (int64_t)b - 1, r0 + b - 1));
 #pragma unroll
             for (int t = 0; t < COLS; ++t) car[t] = yr[t];
-            if (has_next) load_blocks(j + 1);   // in flight from here on
+            // in flight from here on; no branch around them, so that the corner is not
+            // waited for together with them (past the last step: nothing but the
+            // dummy address)
+            load_blocks(j + 1);
             if (corner) {
                 const cx vb = ldx<C>(&vs[(b - 1) * E]);
                 cx zc = z;
