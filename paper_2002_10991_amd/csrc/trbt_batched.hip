@@ -107,6 +107,13 @@ __global__ __launch_bounds__(64 * NW) void k_blocked_batched(const BProb* __rest
                                                              unsigned* __restrict__ err)
 {
     constexpr int D = ring_depth<NB, CPLX, CT>();
+    // Real strips of two column tiles at nbw = 32 run faster in a large batch
+    // when the loads in flight are waited for at the blocks' boundaries: 64
+    // problems of n = 512 .. 4096 take 48.7 ms instead of 53.8, 20 of them 15.0
+    // either way.  The other forms lose by it (nbw = 64: 40 problems of n = 300
+    // .. 1800 2.67 -> 2.82 ms; nbw = 16: 24 of n = 400 .. 2400 7.55 -> 7.62;
+    // complex nbw = 32: 24 of n = 400 .. 1600 4.40 -> 5.76).
+    constexpr bool AHEAD = CPLX || CT == 1 || NB != 32;
     __shared__ StripLds<NB, CT, CPLX, NW> S;
     __shared__ int s_task;
     const int home = blockIdx.x % NXCD;
@@ -131,7 +138,7 @@ __global__ __launch_bounds__(64 * NW) void k_blocked_batched(const BProb* __rest
         if (task < 0) return;
         const BTask tk = tasks[task];
         const BProb& P = probs[tk.prob];
-        blocked_strip<NB, CT, CPLX, D, NW, false, rotating_window<NB, CPLX>()>(
+        blocked_strip<NB, CT, CPLX, D, NW, false, rotating_window<NB, CPLX>(), false, AHEAD>(
             P.n, P.nev, P.ws, P.Z, P.ldz, err, tk.strip, S);
         __syncthreads();
     }

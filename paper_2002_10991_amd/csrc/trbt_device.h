@@ -788,8 +788,11 @@ __device__ inline void lds_get(Tile<CPLX> (&t)[CT], const double* __restrict__ s
 //   ckpt[((((b * NT + q) * nstrips + strip) * NC + plane) * 4 + e) * 64 + lane]
 // b = the block's slot-major index, q = tile of the window, plane = real or
 // imaginary part (NC = 2 complex, 1 real), e = element.
+//
+// AHEAD = false: no refills past a slot's last block, which has the loads in
+// flight waited for at the blocks' boundaries (see the batched kernel).
 template <int NB, int CT, bool CPLX, int D, int NW, bool CKPT = false, bool ROT = CPLX,
-          bool SG = false>
+          bool SG = false, bool AHEAD = true>
 __device__ __attribute__((always_inline)) inline void blocked_strip(int64_t n, int64_t nev, const double* __restrict__ wsb,
                                      double* __restrict__ Z, int64_t ldz,
                                      unsigned* __restrict__ err, int64_t strip,
@@ -910,7 +913,7 @@ __device__ __attribute__((always_inline)) inline void blocked_strip(int64_t n, i
                 const int slot = c % D;
                 if (c + D < NCH)
                     load_chunk<CPLX, D>(ops, boff, c + D, lane, ring_re, ring_im, slot);
-                else
+                else if (AHEAD || has_next)
                     load_chunk<CPLX, D>(ops, bnext, c + D - NCH, lane, ring_re, ring_im, slot);
                 __builtin_amdgcn_sched_barrier(0);
             };
