@@ -46,28 +46,26 @@ constexpr double TD_CLUSTER = 1e-6;
 constexpr double TD_E2MIN = 1e-40;
 
 // e2[k] = max((s e[k])^2, TD_E2MIN), re[k] = 1 / (s e[k]) (0 for 0) with s the power of
-// two that brings ||T|| into [1/2, 1); bounds[0..1] = Gershgorin interval,
-// bounds[2] = norm estimate (max row sum), bounds[3] = width below which
-// an interval is done, bounds[4] = s.  One workgroup.
+// two that brings ||T|| into [1/2, 1) (as far as s is a number); bounds[0..1] = Gershgorin
+// interval of the scaled T, bounds[2] = norm estimate (max row sum) of T, bounds[3] = s.
+// One workgroup.
 __global__ __launch_bounds__(256) void k_td_prep(int64_t n, const double* __restrict__ d,
                                                  const double* __restrict__ e,
                                                  double* __restrict__ e2,
                                                  double* __restrict__ re,
                                                  double* __restrict__ bounds)
 {
-    __shared__ double lo_s[256], hi_s[256], nm_s[256], em_s[256];
-    double lo = INFINITY, hi = -INFINITY, nm = 0.0, em = 0.0;
+    __shared__ double lo_s[256], hi_s[256], nm_s[256];
+    double lo = INFINITY, hi = -INFINITY, nm = 0.0;
     for (int64_t k = threadIdx.x; k < n; k += 256) {
         const double a = k > 0 ? fabs(e[k - 1]) : 0.0, b = k + 1 < n ? fabs(e[k]) : 0.0;
         lo = fmin(lo, d[k] - a - b);
         hi = fmax(hi, d[k] + a + b);
         nm = fmax(nm, fabs(d[k]) + a + b);
-        em = fmax(em, b * b);
     }
     lo_s[threadIdx.x] = lo;
     hi_s[threadIdx.x] = hi;
     nm_s[threadIdx.x] = nm;
-    em_s[threadIdx.x] = em;
     for (int h = 128; h > 0; h /= 2) {
         __syncthreads();
         if (threadIdx.x < h) {
@@ -75,25 +73,24 @@ __global__ __launch_bounds__(256) void k_td_prep(int64_t n, const double* __rest
             lo_s[threadIdx.x] = fmin(lo_s[threadIdx.x], lo_s[o]);
             hi_s[threadIdx.x] = fmax(hi_s[threadIdx.x], hi_s[o]);
             nm_s[threadIdx.x] = fmax(nm_s[threadIdx.x], nm_s[o]);
-            em_s[threadIdx.x] = fmax(em_s[threadIdx.x], em_s[o]);
         }
     }
     __syncthreads();
     lo = lo_s[0];
     hi = hi_s[0];
     nm = nm_s[0] > 0.0 ? nm_s[0] : 1.0;
-    em = em_s[0];
     int ex;
     (void)frexp(nm, &ex);
-    const double s = ldexp(1.0, ex < -1000 ? 1000 : -ex);
+    const double s = ldexp(1.0, ex < -1022 ? 1022 : -ex);
     if (threadIdx.x == 0) {
         const double eps = 2.220446049250313e-16;
-        const double pad = 2.0 * eps * fmax(fabs(lo), fabs(hi)) + 2.0 * eps * n * nm + 1e-300;
+        lo *= s;
+        hi *= s;
+        const double pad = 2.0 * eps * fmax(fabs(lo), fabs(hi)) + 2.0 * eps * n * (nm_s[0] * s) + 1e-300;
         bounds[0] = lo - pad;
         bounds[1] = hi + pad;
         bounds[2] = nm;
-        bounds[3] = fmax(2.2250738585072014e-308 * fmax(em, 1.0), 1e-290);
-        bounds[4] = s;
+        bounds[3] = s;
     }
     for (int64_t k = threadIdx.x; k + 1 < n; k += 256) {
         const double es = e[k] * s;
@@ -174,7 +171,7 @@ __device__ inline int td_count(int n, const double* __restrict__ d,
     return cnt;
 }
 
-// eigenvalue i (0-based, ascending) by multisection: MS consecutive lanes share
+// eigenvalue i (0-based, ascending) of the scaled T by multisection: MS consecutive lanes share
 // one eigenvalue and evaluate the Sturm count at MS interior points of its
 // interval, x_k = lo + (hi - lo)(k+1)/(MS+1); the new interval is
 // [x_{k*-1}, x_{k*}] for the first point k* with count > i, read from the
@@ -193,14 +190,14 @@ __global__ __launch_bounds__(TD_THREADS) void k_td_bisect(int64_t n, int64_t nev
     const int gbit = (threadIdx.x & 63) & ~(MS - 1);   // the group's first lane in the wave
     if (i >= nev) return;   // whole groups leave together
     double lo = bounds[0], hi = bounds[1];
-    const double done = bounds[3], s = bounds[4];
+    const double s = bounds[3];
     const double eps = 2.220446049250313e-16;
     // invariant: count(lo) <= i < count(hi)
     for (int it = 0; it < 100; ++it) {
-        if (hi - lo <= 4.0 * eps * fmax(fabs(lo), fabs(hi)) + done) break;
+        if (hi - lo <= 4.0 * eps * fmax(fabs(lo), fabs(hi)) + 1e-290) break;
         const double step = (hi - lo) / (MS + 1);
         const double x = lo + step * (k + 1);
-        const bool above = td_count((int)n, d, e2, s, x * s) > i;
+        const bool above = td_count((int)n, d, e2, s, x) > i;
         const uint64_t grp = (__ballot(above) >> gbit) & (~0ull >> (64 - MS));
         double nlo = lo, nhi = hi;
         if (grp) {
@@ -214,7 +211,7 @@ __global__ __launch_bounds__(TD_THREADS) void k_td_bisect(int64_t n, int64_t nev
         lo = nlo;
         hi = nhi;
     }
-    if (k == 0) w[i] = 0.5 * (lo + hi);
+    if (k == 0) w[i] = 0.5 * (lo + hi) / s;
 }
 
 // a fixed pseudo-random start in [-1, 1): a 32-bit integer hash (two rounds of
@@ -274,7 +271,7 @@ __global__ __launch_bounds__(TD_THREADS) void k_td_invit(int64_t n64, int64_t ne
     const int64_t i = (int64_t)blockIdx.x * TD_THREADS + threadIdx.x;
     if (i >= nev) return;
     const int n = (int)n64;
-    const double s = bounds[4];
+    const double s = bounds[3];
     const double lam = w[i] * s;
     const double tiny = 2.220446049250313e-16 * (bounds[2] * s);
     X += i;
