@@ -42,10 +42,8 @@ constexpr int TD_THREADS = 64;
 // cluster, whose vectors are orthonormalised together afterwards; outside
 // clusters the angle error of inverse iteration is below about eps / TD_CLUSTER
 constexpr double TD_CLUSTER = 1e-6;
-// floor of the squared off-diagonals of the scaled T in the Sturm counts
-constexpr double TD_E2MIN = 1e-40;
 
-// e2[k] = max((s e[k])^2, TD_E2MIN), re[k] = 1 / (s e[k]) (0 for 0) with s the power of
+// e2[k] = (s e[k])^2, re[k] = 1 / (s e[k]) (0 for 0) with s the power of
 // two that brings ||T|| into [1/2, 1) (as far as s is a number); bounds[0..1] = Gershgorin
 // interval of the scaled T, bounds[2] = norm estimate (max row sum) of T, bounds[3] = s.
 // One workgroup.
@@ -94,7 +92,7 @@ __global__ __launch_bounds__(256) void k_td_prep(int64_t n, const double* __rest
     }
     for (int64_t k = threadIdx.x; k + 1 < n; k += 256) {
         const double es = e[k] * s;
-        e2[k] = fmax(es * es, TD_E2MIN);
+        e2[k] = es * es;
         re[k] = es != 0.0 ? 1.0 / es : 0.0;
     }
 }
@@ -107,12 +105,15 @@ __global__ __launch_bounds__(256) void k_td_prep(int64_t n, const double* __rest
 // 4096 lowest at n = 8192; now 57 and 2.7, most of them waits for the scalar
 // loads of d and e^2).
 //
-// The last two minors are brought back to [1/2, 1) every TD_CHUNK steps.  They
-// cannot both vanish in between: two steps leave at least the smallest
-// e^2, TD_E2MIN, of them (a change of T by 1e-20 ||T||), and none grows by more
-// than 3 a step.  A minor that is exactly zero counts once whichever sign it
+// The last two minors are brought back to [1/2, 1) every TD_CHUNK steps; none grows by
+// more than 3 a step.  They may vanish, though: a zero minor before a zero
+// off-diagonal (x an eigenvalue of a block that is coupled to nothing) leaves only
+// zeros, and many small factors leave the range.  A chunk that ends with both below
+// TD_SMALL, so that rounding at the end of the range might count, is done again by
+// the pivots.  Otherwise a minor that is exactly zero counts once whichever sign it
 // gets, its neighbours' signs being opposite.
 constexpr int TD_CHUNK = 8;
+constexpr double TD_SMALL = 1e-200, TD_PIVMIN = 1e-290;
 
 __device__ inline int td_count(int n, const double* __restrict__ d,
                                const double* __restrict__ e2, double s, double x)
@@ -126,6 +127,22 @@ __device__ inline int td_count(int n, const double* __restrict__ d,
         p = r;
         bits = __builtin_amdgcn_alignbit(bits, (unsigned)(__builtin_bit_cast(uint64_t, r) >> 32), 31);
     };
+    // rows k0 .. k1-1 by the pivots t_k = d_k - x - e_{k-1}^2 / t_{k-1}, from the minors
+    // p0, q0 and the count c0 before them; a pivot of zero counts as negative
+    auto pivots = [&](int k0, int k1, double p0, double q0, int c0) {
+        double t = p0 / q0;
+        t = copysign(fmax(fabs(t), TD_PIVMIN), t);
+#pragma unroll 1
+        for (int k = k0; k < k1; ++k) {
+            t = fma(d[k], s, -x) - e2[k - 1] / t;
+            if (fabs(t) < TD_PIVMIN) t = -TD_PIVMIN;
+            c0 += t < 0.0;
+        }
+        cnt = c0;
+        q = 1.0;
+        p = t;
+        bits = t < 0.0;
+    };
     // whole chunks, each loaded (scalar loads: the same for every lane) while the
     // one before is worked on
     struct Chunk {
@@ -138,10 +155,14 @@ __device__ inline int td_count(int n, const double* __restrict__ d,
             c.e[i] = e2[k - 1 + i];
         }
     };
-    auto work = [&](const Chunk& c) {
+    auto work = [&](const Chunk& c, int j) {
+        const double p0 = p, q0 = q;
+        const int c0 = cnt;
 #pragma unroll
         for (int i = 0; i < TD_CHUNK; ++i) step(c.d[i], c.e[i]);
         cnt += __builtin_popcount((bits ^ (bits >> 1)) & ((1u << TD_CHUNK) - 1));
+        if (fmax(fabs(p), fabs(q)) < TD_SMALL)
+            pivots(1 + j * TD_CHUNK, 1 + (j + 1) * TD_CHUNK, p0, q0, c0);
         const int ex = __builtin_amdgcn_frexp_exp(fmax(fabs(p), fabs(q)));
         p = __builtin_amdgcn_ldexp(p, -ex);
         q = __builtin_amdgcn_ldexp(q, -ex);
@@ -153,21 +174,23 @@ __device__ inline int td_count(int n, const double* __restrict__ d,
     for (; j + 2 < m; j += 2) {
         load(b, 1 + (j + 1) * TD_CHUNK);
         __builtin_amdgcn_sched_barrier(0);   // (or the loads would sink to their use)
-        work(a);
+        work(a, j);
         load(a, 1 + (j + 2) * TD_CHUNK);
         __builtin_amdgcn_sched_barrier(0);
-        work(b);
+        work(b, j + 1);
     }
-    if (j < m) work(a);
+    if (j < m) work(a, j);
     if (j + 1 < m) {
         load(b, 1 + (j + 1) * TD_CHUNK);
-        work(b);
+        work(b, j + 1);
     }
-    int k = 1 + m * TD_CHUNK;
-    for (; k < n; ++k) {
+    const double p0 = p, q0 = q;
+    const int k0 = 1 + m * TD_CHUNK, c0 = cnt;
+    for (int k = k0; k < n; ++k) {
         step(d[k], e2[k - 1]);
         cnt += (bits ^ (bits >> 1)) & 1;
     }
+    if (fmax(fabs(p), fabs(q)) < TD_SMALL) pivots(k0, n, p0, q0, c0);
     return cnt;
 }
 
