@@ -108,12 +108,31 @@ __global__ __launch_bounds__(256) void k_td_prep(int64_t n, const double* __rest
 // The last two minors are brought back to [1/2, 1) every TD_CHUNK steps; none grows by
 // more than 3 a step.  They may vanish, though: a zero minor before a zero
 // off-diagonal (x an eigenvalue of a block that is coupled to nothing) leaves only
-// zeros, and many small factors leave the range.  A chunk that ends with both below
-// TD_SMALL, so that rounding at the end of the range might count, is done again by
-// the pivots.  Otherwise a minor that is exactly zero counts once whichever sign it
-// gets, its neighbours' signs being opposite.
+// zeros, and many small factors leave the range.  A count in which a chunk ends with
+// both below TD_SMALL, so that rounding at the end of the range might matter, is
+// done again by the pivots (a branch inside the loop, to do the one chunk again,
+// takes 3.3 ms for the 2.7 at n = 8192, where no chunk is: the loads made ahead are
+// waited for at it).  Otherwise a minor that is exactly zero counts once whichever
+// sign it gets, its neighbours' signs being opposite.
 constexpr int TD_CHUNK = 8;
+constexpr int TD_EXMIN = -664;   // of TD_SMALL
 constexpr double TD_SMALL = 1e-200, TD_PIVMIN = 1e-290;
+
+// The same count by the pivots t_k = d_k - x - e_{k-1}^2 / t_{k-1}, a zero one counted as
+// negative
+__device__ inline int td_count_pivots(int n, const double* __restrict__ d,
+                                      const double* __restrict__ e2, double s, double x)
+{
+    int cnt = 0;
+    double t = INFINITY;
+#pragma unroll 1
+    for (int k = 0; k < n; ++k) {
+        t = fma(d[k], s, -x) - (k > 0 ? e2[k - 1] / t : 0.0);
+        if (fabs(t) < TD_PIVMIN) t = -TD_PIVMIN;
+        cnt += t < 0.0;
+    }
+    return cnt;
+}
 
 __device__ inline int td_count(int n, const double* __restrict__ d,
                                const double* __restrict__ e2, double s, double x)
@@ -127,22 +146,6 @@ __device__ inline int td_count(int n, const double* __restrict__ d,
         p = r;
         bits = __builtin_amdgcn_alignbit(bits, (unsigned)(__builtin_bit_cast(uint64_t, r) >> 32), 31);
     };
-    // rows k0 .. k1-1 by the pivots t_k = d_k - x - e_{k-1}^2 / t_{k-1}, from the minors
-    // p0, q0 and the count c0 before them; a pivot of zero counts as negative
-    auto pivots = [&](int k0, int k1, double p0, double q0, int c0) {
-        double t = p0 / q0;
-        t = copysign(fmax(fabs(t), TD_PIVMIN), t);
-#pragma unroll 1
-        for (int k = k0; k < k1; ++k) {
-            t = fma(d[k], s, -x) - e2[k - 1] / t;
-            if (fabs(t) < TD_PIVMIN) t = -TD_PIVMIN;
-            c0 += t < 0.0;
-        }
-        cnt = c0;
-        q = 1.0;
-        p = t;
-        bits = t < 0.0;
-    };
     // whole chunks, each loaded (scalar loads: the same for every lane) while the
     // one before is worked on
     struct Chunk {
@@ -155,15 +158,13 @@ __device__ inline int td_count(int n, const double* __restrict__ d,
             c.e[i] = e2[k - 1 + i];
         }
     };
-    auto work = [&](const Chunk& c, int j) {
-        const double p0 = p, q0 = q;
-        const int c0 = cnt;
+    int least = 0;   // exponent of the largest minor at the chunks' ends, the smallest of them
+    auto work = [&](const Chunk& c) {
 #pragma unroll
         for (int i = 0; i < TD_CHUNK; ++i) step(c.d[i], c.e[i]);
         cnt += __builtin_popcount((bits ^ (bits >> 1)) & ((1u << TD_CHUNK) - 1));
-        if (fmax(fabs(p), fabs(q)) < TD_SMALL)
-            pivots(1 + j * TD_CHUNK, 1 + (j + 1) * TD_CHUNK, p0, q0, c0);
         const int ex = __builtin_amdgcn_frexp_exp(fmax(fabs(p), fabs(q)));
+        least = ex < least ? ex : least;   // (two zeros stay zeros to the end)
         p = __builtin_amdgcn_ldexp(p, -ex);
         q = __builtin_amdgcn_ldexp(q, -ex);
     };
@@ -174,23 +175,22 @@ __device__ inline int td_count(int n, const double* __restrict__ d,
     for (; j + 2 < m; j += 2) {
         load(b, 1 + (j + 1) * TD_CHUNK);
         __builtin_amdgcn_sched_barrier(0);   // (or the loads would sink to their use)
-        work(a, j);
+        work(a);
         load(a, 1 + (j + 2) * TD_CHUNK);
         __builtin_amdgcn_sched_barrier(0);
-        work(b, j + 1);
+        work(b);
     }
-    if (j < m) work(a, j);
+    if (j < m) work(a);
     if (j + 1 < m) {
         load(b, 1 + (j + 1) * TD_CHUNK);
-        work(b, j + 1);
+        work(b);
     }
-    const double p0 = p, q0 = q;
-    const int k0 = 1 + m * TD_CHUNK, c0 = cnt;
-    for (int k = k0; k < n; ++k) {
+    for (int k = 1 + m * TD_CHUNK; k < n; ++k) {
         step(d[k], e2[k - 1]);
         cnt += (bits ^ (bits >> 1)) & 1;
     }
-    if (fmax(fabs(p), fabs(q)) < TD_SMALL) pivots(k0, n, p0, q0, c0);
+    if (least < TD_EXMIN || fmax(fabs(p), fabs(q)) < TD_SMALL)
+        return td_count_pivots(n, d, e2, s, x);
     return cnt;
 }
 
