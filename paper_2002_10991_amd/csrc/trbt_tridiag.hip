@@ -506,16 +506,112 @@ __global__ __launch_bounds__(TD_THREADS) void k_td_invit(int64_t n64, int64_t ne
 // work).  Vectors in the output Z (column-major, vector j = Z[j * ldz ..],
 // contiguous, so the workgroup's threads read consecutive rows), already
 // unit.
-__global__ __launch_bounds__(256) void k_td_ortho(int64_t n, int64_t nev,
-                                                  const double* __restrict__ w,
-                                                  const double* __restrict__ bounds,
-                                                  double* __restrict__ Z, int64_t ldz)
+//
+// A vector of which the subtractions leave less than TD_LEFT (of its square)
+// held little that its predecessors did not: what is left of it carries their
+// rounding, 1 / sqrt(TD_LEFT) times as large.  It gets one more step of inverse
+// iteration from there, with the factors that k_td_invit left, which brings up
+// what belongs to its eigenvalue, and is orthonormalised again.  (Four equal
+// random blocks joined by 1e-20 .. 1e-8: 9 of 100 had residuals over 1e-13 ||T||,
+// up to 8e-12; none with it.  A cluster of m random vectors needs it for about
+// sqrt(m TD_LEFT) of them, 0.2 at m = 256.)
+constexpr int TD_OT = 256;          // threads
+constexpr double TD_LEFT = 1e-2;
+constexpr int TD_TRIES = 3;
+
+struct TdStage {   // TD_OT rows on their way through LDS
+    double x[TD_OT], v[TD_OT + 1], d[TD_OT], e[TD_OT + 1], re[TD_OT];
+    int sw[TD_OT + 1];
+};
+
+// x <- (T - lambda I)^{-1} z (scaled T), by the factors V, B of that vector: the
+// workgroup moves the rows, one thread runs the two substitutions.
+__device__ inline void td_solve(int n, int64_t nev, const double* __restrict__ d,
+                                const double* __restrict__ e, const double* __restrict__ re,
+                                double s, double lam, const double* __restrict__ V,
+                                const uint32_t* __restrict__ B, const double* __restrict__ z,
+                                double* __restrict__ x, TdStage& S)
 {
-    // one partial per wave, double-buffered by call parity: each thread only
-    // ever touches its own rows of Z (r = tid mod 256), so the sums are the
-    // only exchange, and one barrier per sum suffices (a wave can reach the
-    // next sum's writes only after every wave has passed this one's barrier)
+    const int tid = threadIdx.x;
+    auto swapped = [&](int k) { return k >= 0 && k < n && (B[(int64_t)(k >> 5) * nev] >> (k & 31) & 1); };
+    auto ev = [&](int k) { return k + 1 < n ? e[k] * s : 0.0; };
+    const int last = (n - 1) / TD_OT * TD_OT;
+    double carry = 0.0, l = 0.0;
+    int sw = 0;   // of the row before
+    for (int k0 = 0; k0 <= last; k0 += TD_OT) {
+        const int k = k0 + tid;
+        if (k < n) {
+            S.x[tid] = z[k];
+            S.v[tid] = V[(int64_t)k * nev];
+            S.e[tid] = ev(k);
+            S.sw[tid] = swapped(k);
+        }
+        __syncthreads();
+        if (tid == 0) {
+            for (int t = 0; t < TD_OT && k0 + t < n; ++t) {
+                const double y = S.x[t];
+                S.x[t] = sw ? y : carry;   // of row k0 + t - 1
+                carry = sw ? fma(-l, y, carry) : fma(-l, carry, y);
+                sw = S.sw[t];
+                l = sw ? S.v[t] : S.e[t] * S.v[t];
+            }
+        }
+        __syncthreads();
+        if (k > 0 && k < n) x[k - 1] = S.x[tid];
+    }
+    if (tid == 0) x[n - 1] = carry;
+    double x1 = 0.0, x2 = 0.0;
+    for (int k0 = last; k0 >= 0; k0 -= TD_OT) {
+        const int k = k0 + tid;
+        __syncthreads();
+        if (k < n) {
+            S.x[tid] = x[k];
+            S.v[tid + 1] = V[(int64_t)k * nev];
+            S.d[tid] = k + 1 < n ? fma(d[k + 1], s, -lam) : 0.0;
+            S.re[tid] = k + 1 < n ? re[k] : 0.0;
+            S.sw[tid + 1] = swapped(k);
+        }
+        S.e[tid] = ev(k);
+        if (tid == 0) {
+            S.e[TD_OT] = ev(k0 + TD_OT);
+            S.v[0] = k0 > 0 ? V[(int64_t)(k0 - 1) * nev] : 0.0;
+            S.sw[0] = swapped(k0 - 1);
+        }
+        __syncthreads();
+        if (tid == 0) {
+            for (int t = (n - k0 < TD_OT ? n - k0 : TD_OT) - 1; t >= 0; --t) {
+                const bool su = S.sw[t + 1];
+                const double u1 = su ? S.d[t] : S.sw[t] ? -S.v[t] * S.e[t] : S.e[t];
+                const double u2 = su ? S.e[t + 1] : 0.0;
+                const double xk = fma(-u1, x1, fma(-u2, x2, S.x[t])) * (su ? S.re[t] : S.v[t + 1]);
+                S.x[t] = xk;
+                x2 = x1;
+                x1 = xk;
+            }
+        }
+        __syncthreads();
+        if (k < n) x[k] = S.x[tid];
+    }
+    __syncthreads();
+}
+
+__global__ __launch_bounds__(TD_OT) void k_td_ortho(int64_t n, int64_t nev,
+                                                    const double* __restrict__ d,
+                                                    const double* __restrict__ e,
+                                                    const double* __restrict__ re,
+                                                    const double* __restrict__ w,
+                                                    const double* __restrict__ bounds,
+                                                    const double* __restrict__ V,
+                                                    const uint32_t* __restrict__ B,
+                                                    double* __restrict__ X,
+                                                    double* __restrict__ Z, int64_t ldz)
+{
+    // one partial per wave, double-buffered by call parity: outside td_solve each
+    // thread only ever touches its own rows of Z (r = tid mod TD_OT), so the sums
+    // are the only exchange, and one barrier per sum suffices (a wave can reach
+    // the next sum's writes only after every wave has passed this one's barrier)
     __shared__ double red[2][4];
+    __shared__ TdStage S;
     const int64_t i = blockIdx.x;
     const double thr = TD_CLUSTER * bounds[2];
     if (i > 0 && w[i] - w[i - 1] <= thr) return;            // not a cluster start
@@ -530,25 +626,46 @@ __global__ __launch_bounds__(256) void k_td_ortho(int64_t n, int64_t nev,
         parity ^= 1;
         return s;
     };
+    auto square = [&](const double* v) {
+        double p = 0.0;
+        for (int64_t r = tid; r < n; r += TD_OT) p = fma(v[r], v[r], p);
+        return block_sum(p);
+    };
     for (int64_t j = i + 1; j < nev && w[j] - w[j - 1] <= thr; ++j) {
         double* __restrict__ zj = Z + j * ldz;
-        // once, and again where little of the (unit) vector was left: what the
-        // subtractions leave is orthogonal to eps over that little
-        double left = 0.0;
-        for (int pass = 0; pass == 0 || (pass == 1 && left < 1e-4); ++pass) {
+        // takes z_i .. z_{j-1} out of z_j; what is left of its square
+        auto reduce = [&]() {
             for (int64_t m = i; m < j; ++m) {
                 const double* __restrict__ zm = Z + m * ldz;
                 double p = 0.0;
-                for (int64_t r = tid; r < n; r += 256) p = fma(zj[r], zm[r], p);
+                for (int64_t r = tid; r < n; r += TD_OT) p = fma(zj[r], zm[r], p);
                 const double dt = block_sum(p);
-                for (int64_t r = tid; r < n; r += 256) zj[r] = fma(-dt, zm[r], zj[r]);
+                for (int64_t r = tid; r < n; r += TD_OT) zj[r] = fma(-dt, zm[r], zj[r]);
             }
-            double p = 0.0;
-            for (int64_t r = tid; r < n; r += 256) p = fma(zj[r], zj[r], p);
-            left = block_sum(p);
+            return square(zj);
+        };
+        for (int tries = 0;; ++tries) {
+            // once, and again where little of the (unit) vector was left: what the
+            // subtractions leave is orthogonal to eps over that little
+            const double first = reduce();
+            double left = first < TD_LEFT ? reduce() : first;
+            if (!(left > 0.0)) {   // nothing: another start
+                for (int64_t r = tid; r < n; r += TD_OT)
+                    zj[r] = td_start((uint32_t)(nev + j), (uint32_t)r);
+                left = reduce();
+            }
+            const double inv = 1.0 / sqrt(left);
+            for (int64_t r = tid; r < n; r += TD_OT) zj[r] *= inv;
+            if (first >= TD_LEFT || tries == TD_TRIES) break;
+            double* __restrict__ xj = X + j * n;   // (the iterates are in Z by now)
+            __syncthreads();
+            td_solve((int)n, nev, d, e, re, bounds[3], td_shift(j, nev, w, bounds).lam,
+                     V + j, B + j, zj, xj, S);
+            const double ss = square(xj);
+            if (!(ss > 0.0 && ss < 1e300)) break;
+            const double xinv = 1.0 / sqrt(ss);
+            for (int64_t r = tid; r < n; r += TD_OT) zj[r] = xj[r] * xinv;
         }
-        const double inv = 1.0 / sqrt(left);
-        for (int64_t r = tid; r < n; r += 256) zj[r] *= inv;
     }
 }
 
@@ -653,8 +770,9 @@ int trbt_tridiag_eigh_d(int64_t n, int64_t nev, const double* d, const double* e
                        (const double*)bounds, (const double*)w, X, V, B, sc);
     hipLaunchKernelGGL(k_td_out, dim3((unsigned)((n + 31) / 32), (unsigned)((nev + 31) / 32)),
                        dim3(256), 0, st, n, nev, (const double*)X, (const double*)sc, Z, ldz);
-    hipLaunchKernelGGL(k_td_ortho, dim3((unsigned)nev), dim3(256), 0, st, n, nev,
-                       (const double*)w, (const double*)bounds, Z, ldz);
+    hipLaunchKernelGGL(k_td_ortho, dim3((unsigned)nev), dim3(TD_OT), 0, st, n, nev,
+                       d, e, (const double*)re, (const double*)w, (const double*)bounds,
+                       (const double*)V, (const uint32_t*)B, X, Z, ldz);
     return hipGetLastError() == hipSuccess ? TRBT_SUCCESS : TRBT_ERR_HIP;
 }
 

@@ -57,3 +57,13 @@ def test_entries_over_many_orders(seed):
            n, "entries 1e-40 .. 1")
     _check(10.0 ** -np.linspace(0, 30, n) * rng.standard_normal(n),
            10.0 ** -np.linspace(1, 31, n - 1) * rng.standard_normal(n - 1), n, "graded")
+
+
+@pytest.mark.parametrize("seed", range(24))
+def test_joined_equal_blocks(seed):
+    """Four equal random blocks joined by couplings around rounding."""
+    rng = np.random.default_rng(seed)
+    m = 25
+    d, e = rng.standard_normal(m), rng.standard_normal(m - 1)
+    for c in (0.0, 1e-18, 1e-15, 1e-12, 1e-9):
+        _check(np.tile(d, 4), np.concatenate([e, [c], e, [c], e, [c], e]), 4 * m, f"blocks, {c}")
