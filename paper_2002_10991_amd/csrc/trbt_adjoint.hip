@@ -305,10 +305,11 @@ __device__ __attribute__((always_inline)) inline void adj_sweep_strip(
     Tile<CPLX> g[NT];
     // a window tile from G; real ones that lie inside have no select behind
     // their loads (a select waits for them: n = 4096, nbw = 64, nev = 2048
-    // takes 13.0 ms instead of 12.5; complex blocks are 2% faster with)
+    // takes 13.0 ms instead of 12.5; complex blocks are 2% faster with, real ones
+    // of nbw <= 32 up to 4%)
     auto fetch = [&](Tile<CPLX>& x, int64_t r) {
         const bool inside = cols_inside && r >= 0 && r + 16 <= n;
-        if constexpr (CPLX) {
+        if constexpr (CPLX || NB <= 32) {
             load_tile<CPLX>(x, G, ldg, n, nev, r + rsub, col, inside, pred_global);
         } else {
             issue_tile<CPLX>(x, G, ldg, n, nev, r + rsub, col, pred_global);

@@ -840,9 +840,12 @@ __device__ __attribute__((always_inline)) inline void blocked_strip(int64_t n, i
 
     // a window tile from Z; a real one that crosses the matrix's edge is
     // masked later, by its user (complex blocks have no registers for that:
-    // 2% slower at n = 1500, nbw = 32)
+    // 2% slower at n = 1500, nbw = 32; nor does it pay with the checkpoints' stores in
+    // short blocks: forward and adjoint 6.99 instead of 6.46 ms at n = 3000, nbw =
+    // 16, nev = 1000, 1.77 and 1.71 at n = 1500, nbw = 32, nev = 1500)
+    constexpr bool SELECT = CPLX || (CKPT && NB <= 32);
     auto fetch = [&](Tile<CPLX>& x, int64_t row0, int64_t col, bool inside) {
-        if constexpr (CPLX)
+        if constexpr (SELECT)
             load_tile<CPLX>(x, Z, ldz, n, nev, row0, col, inside, pred_global);
         else
             issue_tile<CPLX>(x, Z, ldz, n, nev, row0, col, pred_global);
@@ -868,7 +871,7 @@ __device__ __attribute__((always_inline)) inline void blocked_strip(int64_t n, i
         }
 #pragma unroll
         for (int c = 0; c < D; ++c) load_chunk<CPLX, D>(ops, 0, c, lane, ring_re, ring_im, c);
-        if (!CPLX && !(cols_inside && p0 >= 0 && p0 + 16 * NT <= n)) {
+        if (!SELECT && !(cols_inside && p0 >= 0 && p0 + 16 * NT <= n)) {
 #pragma unroll
             for (int q = 0; q < NT; ++q)
 #pragma unroll
@@ -898,7 +901,7 @@ __device__ __attribute__((always_inline)) inline void blocked_strip(int64_t n, i
                     fetch(znext[c], p0 - 16 + rsub, col_base + 16 * c, inside);
             }
             const bool zedge =
-                !CPLX && !xin && has_next && !(cols_inside && p0 - 16 >= 0 && p0 <= n);
+                !SELECT && !xin && has_next && !(cols_inside && p0 - 16 >= 0 && p0 <= n);
 
             // operand chunk c of this block sits in ring slot c % D; behind
             // its last product the slot is refilled with chunk c + D (running
