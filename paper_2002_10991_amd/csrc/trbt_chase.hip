@@ -338,17 +338,10 @@ __global__ __launch_bounds__(64 * NW) void k_chase(int64_t n, int b,
                 ad[t] = ldx_coh<C>(okd ? cw + t * SNW + rd : bd);
             }
         };
-        // publish step j: every wave waits until its (device-coherent)
-        // stores have completed, the workgroup meets, and one counter
-        // store.  A waiting stage reads the counter, then the band with
-        // device-coherent loads, so it sees every store made before the
-        // counter.  (Agent-scope release and acquire fences would write
-        // back and invalidate the whole L2 of the XCD at every step; one
-        // atomic add per wave instead of the barrier was much slower:
-        // the adds to one address serialise.)
         // (s-1, 0 .. 1) done: a later step's start is covered by the tail of
         // the step before
         if (s > 0) {
+            wait_jitter(s, w);
             if (threadIdx.x == 0) fail_sh = !chase_wait(&prog[s - 1], 2 < Sp ? 2 : Sp, ctl);
             __syncthreads();
             if (fail_sh) return;
@@ -527,9 +520,16 @@ __global__ __launch_bounds__(64 * NW) void k_chase(int64_t n, int b,
                 ahead = __hip_atomic_load(&prog[s - 1], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 
             // publish ahead of the tail (which stores nothing, unless this is
-            // the stage's last step): the last wave waits until every wave's
-            // stores have completed
+            // the stage's last step): every wave waits until its (device-
+            // coherent) stores have completed and says so in LDS, and the last
+            // wave then stores the counter.  A waiting stage reads the counter,
+            // then the band with device-coherent loads, so it sees every store
+            // made before the counter.  (Agent-scope release and acquire fences
+            // would write back and invalidate the whole L2 of the XCD at every
+            // step; one atomic add per wave to the counter in memory was much
+            // slower: the adds to one address serialise.)
             if (has_next) {
+                wait_jitter(w, j);
                 asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
                 if (lane == 0)
                     __hip_atomic_fetch_add(&drained, 1u, __ATOMIC_RELEASE,
@@ -557,6 +557,7 @@ __global__ __launch_bounds__(64 * NW) void k_chase(int64_t n, int b,
             if (s > 0) {
                 const int need = (int)(j + 3 < Sp ? j + 3 : Sp);
                 ++tick;
+                wait_jitter(s, w);
                 if (w == 0) {
                     if (lane == 0) {
                         const bool ok = ahead >= need || chase_wait(&prog[s - 1], need, ctl);
@@ -585,8 +586,8 @@ __global__ __launch_bounds__(64 * NW) void k_chase(int64_t n, int b,
 #pragma unroll
             for (int t = 0; t < COLS; ++t) car[t] = yr[t];
             // in flight from here on; no branch around them, so that the corner is not
-            // waited for together with them (past the last step: nothing but the
-            // dummy address)
+            // waited for together with them (past the last step: the dummy address,
+            // and the diagonal of a single row left over; neither is used)
             load_blocks(j + 1);
             if (corner) {
                 const cx vb = ldx<C>(&vs[(b - 1) * E]);
