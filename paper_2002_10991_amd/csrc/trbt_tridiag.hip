@@ -490,13 +490,14 @@ __global__ __launch_bounds__(TD_THREADS) void k_td_invit(int64_t n64, int64_t ne
         X[(int64_t)(n - 1) * nev] = carry;
     };
 
-    for (double base = shift.floor;; base = full) {
+    double base = shift.floor;
+    for (int tries = 0; tries < 2; ++tries, base = full) {
         factor(base);
         backward(std::true_type{});
         forward();
         big = 0.0;
         backward(std::false_type{});
-        if ((ss > 0.0 && ss < 1e300) || base == full) break;
+        if (ss > 0.0 && ss < 1e300) break;
     }
     sc[i] = sg / sqrt(ss);
 }

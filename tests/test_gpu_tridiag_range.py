@@ -45,3 +45,20 @@ def test_uncoupled_small_entries():
         small = np.sort(np.argsort(np.abs(w))[:m])
         assert np.max(np.abs(w[small] / size - T1)) <= 1e-13 * 4 * np.max(np.abs(T1))
         assert np.max(np.abs(np.delete(w, small) - T2)) <= 1e-13 * 4 * np.max(np.abs(T2))
+
+
+@pytest.mark.parametrize("bad", [np.nan, np.inf, -np.inf])
+def test_not_finite_ends(bad):
+    """Input that has no eigenpairs: the call returns, and says so in its numbers."""
+    rng = np.random.default_rng(4)
+    for where in ("d", "e", "all"):
+        d, e = rng.standard_normal(70), rng.standard_normal(69)
+        if where == "d":
+            d[11] = bad
+        elif where == "e":
+            e[40] = bad
+        else:
+            d[:], e[:] = bad, bad
+        print(f"[gpu] tridiag {bad} in {where}", flush=True)
+        w, Z = _solve(d, e)
+        assert not (np.all(np.isfinite(w)) and np.all(np.isfinite(Z)))
