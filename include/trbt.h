@@ -425,14 +425,18 @@ int trbt_band_to_tridi_z(int64_t n, int nbw, const trbt_z *ab, int64_t ldab, dou
  * real symmetric tridiagonal T = diag(d) + subdiag(e), ascending, and their
  * eigenvectors, computed only for the wanted ones -- eigenvalue i by
  * bisection on the Sturm count, eigenvector i by inverse iteration (pivoted
- * tridiagonal LU, a fixed pseudo-random start, one and a half solves), one GPU thread
- * per eigenpair.  Each eigenvector is normalised with its largest-magnitude
+ * tridiagonal LU with small pivots raised, a fixed pseudo-random start, one and a
+ * half solves), one GPU thread per eigenvector.  Each eigenvector is normalised with its largest-magnitude
  * entry positive (except vectors of a cluster after its orthonormalisation).
  * Accuracy: residuals ||T z - w z|| ~ eps ||T||; the angle between the
  * vectors of eigenvalues a gap apart ~ eps ||T|| / gap; eigenvalues within
  * 1e-6 ||T|| of each other form a cluster whose vectors are orthonormalised
- * together (modified Gram-Schmidt), so degenerate eigenvalues get an
- * orthonormal basis of their eigenspace.
+ * together (modified Gram-Schmidt, with another solve for a vector that depends
+ * on its predecessors), so degenerate eigenvalues get an orthonormal basis of
+ * their eigenspace.  Off-diagonals are taken as they are: a zero one couples
+ * nothing, and the eigenvalues of what it separates are as accurate as on their own.
+ * T is scaled by a power of two inside, so entries may be of any size whose row
+ * sums are finite numbers.
  * For the complex chase's T (every subdiagonal a real beta except e[n-2])
  * pass Re e with its last entry replaced by |e[n-2]| and multiply the last
  * row of Z by e[n-2] / |e[n-2]| afterwards (T = D T_r D^H with

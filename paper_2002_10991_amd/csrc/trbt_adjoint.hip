@@ -872,6 +872,8 @@ __device__ inline void apply_real(double* z, const double* __restrict__ v, doubl
 // [sbot+1, n) before every block, stored row-major (row-contiguous across
 // columns):
 //   ck[(cb_t + r - sbot_t - 1) * nev + c],  cb_t = sum_{t' < t} (n - sbot_t' - 1).
+// The reverse sweep's tape recomputes a block from there with apply_real, whose sums run
+// in another order: its states agree with the forward's to rounding, not bitwise.
 
 constexpr int RCH = 32;   // dv entries reduced per LDS round
 

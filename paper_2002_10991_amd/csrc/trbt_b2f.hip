@@ -530,9 +530,13 @@ __global__ __launch_bounds__(64 * B2F_NW) void k_b2f_apply(
     const int first = blockIdx.x / B2F_ROUND * B2F_ROUND + blockIdx.x % 8;
     const int peers = ((int)gridDim.x - first + 7) / 8 < B2F_ROUND / 8
                           ? ((int)gridDim.x - first + 7) / 8 : B2F_ROUND / 8;
-        // Short passes drift too little to pay for it (real n = 8192: 14.1 ms without,
-    // 14.9 with; real n = 24001, nev = 2001: 163 and 135; complex n = 4096,
-    // nev = 4096: 9.8 and 10.1; complex n = 16384, nev = 4096: 184 and 159).
+    // Short passes drift too little to pay for it, nor do few strips.  Without and
+    // with, nbw = 64, ms (n, nev): real (8192, 8192) 28.1 and 29.7, (12000, 8192)
+    // 62.2 and 62.2, (16384, 4096) 55.1 and 57.2, (20480, 1000) 80.0 and 80.4,
+    // (20480, 4096) 98.0 and 89.8, (24001, 2001) 148 and 126, (28000, 4096) 184 and
+    // 164; complex (3000, 3000) 5.5 and 5.7, (5000, 5000) 30.9 and 30.7, (6144, 1500)
+    // 20.1 and 20.6, (6144, 4096) 23.2 and 23.0, (8192, 4096) 41.6 and 39.9,
+    // (10000, 8000) 134 and 121, (16384, 4096) 184 and 159.
     bool together = n >= (CPLX ? 6144 : 20480) && group < B2F_STEPS && peers > 1;
     auto keep_step = [&](int need) {   // one lane
         atomicAdd(&steps[group], 1);

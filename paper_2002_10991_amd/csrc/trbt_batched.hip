@@ -112,7 +112,8 @@ __global__ __launch_bounds__(64 * NW) void k_blocked_batched(const BProb* __rest
     // problems of n = 512 .. 4096 take 48.7 ms instead of 53.8, 20 of them 15.0
     // either way.  The other forms lose by it (nbw = 64: 40 problems of n = 300
     // .. 1800 2.67 -> 2.82 ms; nbw = 16: 24 of n = 400 .. 2400 7.55 -> 7.62;
-    // complex nbw = 32: 24 of n = 400 .. 1600 4.40 -> 5.76).
+    // complex nbw = 32: 24 of n = 400 .. 1600 4.40 -> 5.76).  Measured only: what
+    // the large batch loses with the loads in flight was not found.
     constexpr bool AHEAD = CPLX || CT == 1 || NB != 32;
     __shared__ StripLds<NB, CT, CPLX, NW> S;
     __shared__ int s_task;
