@@ -824,7 +824,7 @@ __global__ __launch_bounds__(64 * RW, CPLX ? 1 : 2) void k_adj_reduce(
 }
 
 // ==========================================================================
-// Streaming adjoint (any nbw): one lane per column
+// Streaming adjoint (any nbw), reverse sweep: one lane per column
 // ==========================================================================
 __host__ __device__ inline int64_t blk_sbot(int64_t n, int64_t t)
 {
