@@ -25,8 +25,10 @@
 //    into W'_{p-1}, and the next panel starts.
 //
 // What bounds it: the strips re-read the reflectors, every element twice, from
-// L2; at 16 columns that is 4 flops a byte real and 8 complex, and a CU got about
-// 20 bytes a clock out of L2 (12 TB/s over the chip).  Skipping those loads
+// L2; at 16 columns that is 4 flops a byte real and 8 complex.  L2 reads (counted at 128
+// bytes): real n = 8192, nev = 4096 10.7 TB/s over the chip, 17 bytes a clock and CU;
+// complex n = 32768, nev = 8192 7.5 TB/s, half of them from beyond the XCD's L2.
+// Skipping those loads
 // (a timing-only variant) took 10.3 and 125 ms where the kernel takes 14.1
 // and 159 (real n = 8192, complex n = 16384, nev = 4096; the matrix
 // instructions alone 7.7 and 112).  Wider strips would halve the reads and leave

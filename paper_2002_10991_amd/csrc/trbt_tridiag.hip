@@ -163,8 +163,8 @@ __device__ inline int td_count(int n, const double* __restrict__ d,
     auto work = [&](const Chunk& c) {
 #pragma unroll
         for (int i = 0; i < TD_CHUNK; ++i) step(c.d[i], c.e[i]);
-        cnt += __builtin_popcount((bits ^ (bits >> 1)) & ((1u << TD_CHUNK) - 1));
         const int ex = __builtin_amdgcn_frexp_exp(fmax(fabs(p), fabs(q)));
+        cnt += __builtin_popcount((bits ^ (bits >> 1)) & ((1u << TD_CHUNK) - 1));
         least = ex < least ? ex : least;   // (two zeros stay zeros to the end)
         p = __builtin_amdgcn_ldexp(p, -ex);
         q = __builtin_amdgcn_ldexp(q, -ex);
